@@ -22,15 +22,25 @@ FLAGS = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}",
          "-Wall", "-Wno-unused-function", "-I", os.path.join(ROOT, "include"), "-I", CSRC]
 
 
-def sources():
-    return sorted(os.path.join(CSRC, f) for f in os.listdir(CSRC)
-                  if f.endswith((".hip", ".cpp")))
+# compiled once per ring degree, with HCK_LOGN its log2 N
+PER_RING = ("ks_fused.hip", "ntt.hip")
+RINGS = range(11, 18)
 
 
-def _compile(src: str) -> str:
-    obj = os.path.join(OBJ, os.path.basename(src) + ".o")
+def units():
+    """(source, ring or None) of every object, the longest compilations first."""
+    names = sorted(f for f in os.listdir(CSRC) if f.endswith((".hip", ".cpp")))
+    return ([(f, r) for f in PER_RING for r in reversed(RINGS)] +
+            [(f, None) for f in names if f not in PER_RING])
+
+
+def _compile(unit) -> str:
+    name, ring = unit
+    src = os.path.join(CSRC, name)
+    obj = os.path.join(OBJ, name + (f".{ring}" if ring else "") + ".o")
     lang = ["-x", "hip"] if src.endswith(".hip") else []
-    cmd = ["hipcc", *lang, *FLAGS, "-c", src, "-o", obj]
+    ringed = [f"-DHCK_LOGN={ring}"] if ring else []
+    cmd = ["hipcc", *lang, *FLAGS, *ringed, "-c", src, "-o", obj]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError(f"hipcc failed on {src}:\n{r.stdout}\n{r.stderr}")
@@ -39,9 +49,8 @@ def _compile(src: str) -> str:
 
 def build(verbose: bool = False) -> str:
     os.makedirs(OBJ, exist_ok=True)
-    srcs = sources()
-    with concurrent.futures.ThreadPoolExecutor(max_workers=min(8, len(srcs))) as ex:
-        objs = list(ex.map(_compile, srcs))
+    with concurrent.futures.ThreadPoolExecutor(max_workers=8) as ex:
+        objs = list(ex.map(_compile, units()))
     tmp = LIB + ".tmp"
     cmd = ["hipcc", f"--offload-arch={ARCH}", "-shared", "-fPIC", "-o", tmp, *objs,
            "-lpthread"]

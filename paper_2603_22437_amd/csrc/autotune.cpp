@@ -207,7 +207,7 @@ int hck_autotune_ntt(hck_context *ctx, uint32_t rows, int32_t *splits, double *u
     for (int r = 0; r <= 5 && !rc; r++) {
       if (hipEventRecord(e0, ctx->stream) != hipSuccess) rc = check_hip(ctx, hipGetLastError(), "event");
       if (!rc) rc = ntt_forward(ctx, buf, map);
-      if (!rc) rc = ntt_inverse(ctx, buf, map, nullptr);
+      if (!rc) rc = ntt_inverse(ctx, buf, map);
       float ms = 0;
       if (!rc && (hipEventRecord(e1, ctx->stream) != hipSuccess ||
                   hipEventSynchronize(e1) != hipSuccess ||

@@ -115,7 +115,7 @@ LimbMap make_map(const std::vector<std::pair<uint16_t, uint8_t>> &rows, size_t s
 
 int inverse_rows(hck_context *ctx, uint64_t *buf,
                  const std::vector<std::pair<uint16_t, uint8_t>> &rows) {
-  for (size_t s = 0; s < rows.size(); s += kMaxRows) TRY(ntt_inverse(ctx, buf, make_map(rows, s, kMaxRows), nullptr));
+  for (size_t s = 0; s < rows.size(); s += kMaxRows) TRY(ntt_inverse(ctx, buf, make_map(rows, s, kMaxRows)));
   return HCK_OK;
 }
 
@@ -123,6 +123,14 @@ int mont_rows(hck_context *ctx, uint64_t *buf,
               const std::vector<std::pair<uint16_t, uint8_t>> &rows, bool to) {
   for (size_t s = 0; s < rows.size(); s += kMaxRows)
     TRY(launch_to_mont(ctx, buf, make_map(rows, s, kMaxRows), to));
+  return HCK_OK;
+}
+
+// switch-key rows into (or out of) the key switch's form
+int key_form_rows(hck_context *ctx, uint64_t *buf,
+                  const std::vector<std::pair<uint16_t, uint8_t>> &rows, bool to) {
+  for (size_t s = 0; s < rows.size(); s += kMaxRows)
+    TRY(launch_key_form(ctx, buf, make_map(rows, s, kMaxRows), to));
   return HCK_OK;
 }
 
@@ -202,7 +210,7 @@ int export_key_rows(hck_context *ctx, const uint64_t *buf, uint32_t polys, uint6
   TRY(dev_alloc(ctx, &tmp, (size_t)polys * nm * n));
   int rc = launch_copy(ctx, tmp, buf, (size_t)polys * nm * n);
   auto rows = poly_rows(polys, nm, nm, 0);
-  if (!rc) rc = mont_rows(ctx, tmp, rows, false);
+  if (!rc) rc = key_form_rows(ctx, tmp, rows, false);
   if (!rc) rc = inverse_rows(ctx, tmp, rows);
   if (!rc) rc = download(ctx, out, tmp, (size_t)polys * nm * n * 8);
   dev_free(ctx, tmp);
@@ -210,7 +218,7 @@ int export_key_rows(hck_context *ctx, const uint64_t *buf, uint32_t polys, uint6
 }
 
 // swk(s' -> s): digit j = (-a_j s + e_j + [i in D_j] (P mod q_i) s'_i, a_j) on
-// all L+K limbs, stored in evaluation + Montgomery form.  sp_m: s' as
+// all L+K limbs, stored in the key switch's form.  sp_m: s' as
 // evaluation-form Montgomery rows [L+K][N].
 int make_switch_key(hck_context *ctx, const hck_secret_key *sk, const uint64_t *sp_m,
                     const std::string &tag, uint64_t seed, hck_switch_key **out) {
@@ -258,7 +266,7 @@ int make_switch_key(hck_context *ctx, const hck_secret_key *sk, const uint64_t *
       }
       rc = launch_scalar_mac(ctx, b, sp_m, m, sc);
     }
-    if (!rc) rc = mont_rows(ctx, b, poly_rows(2, nm, nm), true);
+    if (!rc) rc = key_form_rows(ctx, b, poly_rows(2, nm, nm), true);
   }
   if (rc) {
     dev_free(ctx, key->data);
@@ -283,7 +291,7 @@ int key_rows_to_internal(hck_context *ctx, uint64_t *buf) {
   const uint32_t nm = ctx->L + ctx->K;
   const auto rows = poly_rows(2 * ctx->dnum, nm, nm, 0);
   TRY(ntt_forward_rows(ctx, buf, rows));
-  return mont_rows(ctx, buf, rows, true);
+  return key_form_rows(ctx, buf, rows, true);
 }
 
 int ct_from_host_async(hck_context *ctx, hck_ciphertext *ct, const uint64_t *host,
@@ -1072,7 +1080,7 @@ int hck_rescale(hck_context *ctx, const hck_ciphertext *a, hck_ciphertext *out) 
   }
   // dropped limb to coefficient form; then per target limb its centred lift,
   // forward transform and (c_i - t) q_l^-1, in two fused passes
-  TRY(ntt_inverse(ctx, last, make_map(lrows, 0), nullptr));
+  TRY(ntt_inverse(ctx, last, make_map(lrows, 0)));
   TRY(rescale_fused(ctx, out->data, a->data, last, lift, level, size));
   out->size = size;
   out->level = level - 1;

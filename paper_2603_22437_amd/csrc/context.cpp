@@ -47,35 +47,122 @@ bool is_prime_u64(uint64_t n) {
 
 // A primitive 2N-th root of unity: psi = x^((q-1)/2N) for the first x >= 3
 // with psi^N = -1 (q prime, q = 1 mod 2N).
-// contiguous-pass twists (ntt_core.h) of one limb for the split 2^log_a x
-// 2^(log_n - log_a): word g R2 + i gets beta_g^i (and beta_g^-i), beta_g =
-// psi^(2 brv_a(g)); pw, ipw hold psi^k, psi^-k for k < N
-void twist_rows(const std::vector<uint64_t> &pw, const std::vector<uint64_t> &ipw, uint64_t q,
-                uint32_t log_n, int log_a, size_t base, std::vector<uint64_t> &ttw,
-                std::vector<uint64_t> &ttws, std::vector<uint64_t> &ittw,
-                std::vector<uint64_t> &ittws) {
-  const uint64_t n = 1ull << log_n;
-  const int log_b = (int)log_n - log_a;
-  for (uint32_t g = 0; g < (1u << log_a); g++) {
-    const uint64_t bg = 2ull * bit_reverse(g, log_a);
-    for (uint32_t i = 0; i < (1u << log_b); i++) {
-      const uint64_t e = bg * i % (2ull * n);   // psi^N = -1
-      const uint64_t f = e < n ? pw[e] : (q - pw[e - n]) % q;
-      const uint64_t fi = e < n ? ipw[e] : (q - ipw[e - n]) % q;
-      const size_t w = base + ((size_t)g << log_b) + i;
-      ttw[w] = f;
-      ttws[w] = h_shoup(f, q);
-      ittw[w] = fi;
-      ittws[w] = h_shoup(fi, q);
-    }
-  }
-}
-
 uint64_t primitive_2n_root(uint64_t q, uint64_t n) {
   for (uint64_t x = 3;; x++) {
     uint64_t psi = h_powmod(x, (q - 1) / (2 * n), q);
     if (h_powmod(psi, n, q) == q - 1) return psi;
   }
+}
+
+// psi^k, k < N, and the same of psi^-1
+struct Powers {
+  std::vector<uint64_t> pw, ipw;
+  uint64_t q, n;
+  Powers(uint64_t q_, uint64_t n_) : pw(n_), ipw(n_), q(q_), n(n_) {
+    const uint64_t psi = primitive_2n_root(q, n), ipsi = h_invmod(psi, q);
+    pw[0] = ipw[0] = 1;
+    for (uint64_t i = 1; i < n; i++) {
+      pw[i] = h_mulmod(pw[i - 1], psi, q);
+      ipw[i] = h_mulmod(ipw[i - 1], ipsi, q);
+    }
+  }
+  // psi^e, psi^-e for any e (psi^N = -1)
+  uint64_t pos(uint64_t e) const { return at(pw, e); }
+  uint64_t neg(uint64_t e) const { return at(ipw, e); }
+
+ private:
+  uint64_t at(const std::vector<uint64_t> &v, uint64_t e) const {
+    e &= 2 * n - 1;
+    return e < n ? v[e] : q - v[e - n];
+  }
+};
+
+int upload_table(hck_context *ctx, void **dst, const void *src, size_t bytes) {
+  if (hipMalloc(dst, bytes) != hipSuccess) {
+    *dst = nullptr;
+    (void)hipGetLastError();
+    return set_error(HCK_ENOMEM, "table allocation failed");
+  }
+  if (hipMemcpy(*dst, src, bytes, hipMemcpyHostToDevice) != hipSuccess)
+    return check_hip(ctx, hipGetLastError(), "table upload");
+  return HCK_OK;
+}
+
+// The tables of the split 2^log_a x 2^(log_n - log_a) (ntt_core.h): word
+// g R2 + i of a limb's twist is psi^((2 brv_a(g) + 1) i); row i's factor of
+// the inverse is N^-1 psi^(-R2 i).
+int make_split(hck_context *ctx, const std::vector<Powers> &pws, int log_a,
+               hck_context::Split *out) {
+  const int log_b = (int)ctx->log_n - log_a;
+  const size_t n = ctx->n, r1 = (size_t)1 << log_a, r2 = (size_t)1 << log_b, nm = pws.size();
+  std::vector<Tw> t(nm * n), it(nm * n), rows(nm * r1);
+  for (size_t m = 0; m < nm; m++) {
+    const Powers &p = pws[m];
+    for (size_t g = 0; g < r1; g++) {
+      const uint64_t step = 2ull * bit_reverse((uint32_t)g, (uint32_t)log_a) + 1;
+      for (size_t i = 0; i < r2; i++) {
+        t[m * n + g * r2 + i] = h_tw(p.pos(step * i), p.q);
+        it[m * n + g * r2 + i] = h_tw(p.neg(step * i), p.q);
+      }
+    }
+    const uint64_t ninv = h_invmod(n % p.q, p.q);
+    for (size_t i = 0; i < r1; i++)
+      rows[m * r1 + i] = h_tw(h_mulmod(ninv, p.neg(r2 * i), p.q), p.q);
+  }
+  hck_context::Split sp;
+  int rc = upload_table(ctx, (void **)&sp.twist, t.data(), t.size() * sizeof(Tw));
+  if (!rc) rc = upload_table(ctx, (void **)&sp.itwist, it.data(), it.size() * sizeof(Tw));
+  if (!rc) rc = upload_table(ctx, (void **)&sp.rows, rows.data(), rows.size() * sizeof(Tw));
+  if (rc) {
+    for (void *p : {(void *)sp.twist, (void *)sp.itwist, (void *)sp.rows})
+      if (p) (void)hipFree(p);
+    return rc;
+  }
+  *out = sp;
+  return HCK_OK;
+}
+
+// The constants of one conversion's sources src[0..na) (moduli) to modulus t,
+// hat(a) = the constant of source a, in rows out[a * stride] and the centring
+// row out[na * stride].  Returns whether the conversion in doubles keeps every
+// column exact (bconv_float): with |v0|, |v1| <= 2^24 + 2^19 (a source in the
+// floating-point range is below 2^50 + 2^44) and v2 < 2^11,
+//   sum |c0 + c1| (2^25 + 2^20) + sum |es| 2^11 <= 2^53,
+//   sum (|c0| + |c1|) (2^24 + 2^19) + sum (|e0| + |es|) 2^11 <= 2^52.
+template <class Hat>
+bool conv_constants(const std::vector<uint64_t> &src, uint64_t t, Hat &&hat, ConvC *out,
+                    size_t stride) {
+  auto halves = [](int64_t c, double *lo, double *hi) {
+    const int64_t h = (c + (1 << 24)) >> 25;
+    *lo = (double)(c - h * (1 << 25));
+    *hi = (double)h;
+  };
+  const uint64_t r64 = h_r64(t), off = ((1ull << 49) + (1ull << 24)) % t;
+  uint64_t k = 0;
+  double cross = 0, mid = 0;
+  for (size_t a = 0; a < src.size(); a++) {
+    const uint64_t c = hat(a);
+    ConvC &o = out[a * stride];
+    o.w = h_mulmod(c, r64, t);
+    o.c0 = o.c1 = o.cs = o.e0 = o.es = 0;
+    if (!h_float_modulus(t)) continue;
+    halves(h_centred(c, t), &o.c0, &o.c1);
+    o.cs = o.c0 + o.c1;
+    k = (uint64_t)(((unsigned __int128)off * c + k) % t);
+    double e1 = 0;
+    if (!h_float_modulus(src[a])) {
+      halves(h_centred(h_mulmod(c, (1ull << 50) % t, t), t), &o.e0, &e1);
+      o.es = o.e0 + e1;
+    }
+    const auto abs = [](double d) { return d < 0 ? -d : d; };
+    cross += abs(o.cs) * ((1 << 25) + (1 << 20)) + abs(o.es) * 2048;
+    mid += (abs(o.c0) + abs(o.c1)) * ((1 << 24) + (1 << 19)) + (abs(o.e0) + abs(o.es)) * 2048;
+  }
+  ConvC &o = out[src.size() * stride];
+  o.w = 0;
+  o.c1 = o.cs = o.e0 = o.es = 0;
+  o.c0 = h_float_modulus(t) ? (double)h_centred(k, t) : 0;
+  return cross <= 9007199254740992.0 && mid <= 4503599627370496.0;
 }
 
 }  // namespace
@@ -320,14 +407,8 @@ int build_context(const hck_params *prm, int device, void *stream, hck_context *
 
   // per-modulus constants and twiddles
   std::vector<ModConst> mc(nm);
-  std::vector<uint64_t> tw((size_t)nm * n), tws((size_t)nm * n), itw((size_t)nm * n),
-      itws((size_t)nm * n);
-  std::vector<uint64_t> ttw((size_t)nm * n), ttws((size_t)nm * n), ittw((size_t)nm * n),
-      ittws((size_t)nm * n);
-  std::vector<uint64_t> pw(n), ipw(n);
-  // contiguous-pass twists (ntt_core.h): word w = g R2 + i of a limb gets
-  // beta_g^i with beta_g = psi^(2 brv_a(g)), a = log2 of the strided radix
-  const int log_a = (ctx->log_n + 1) / 2;
+  std::vector<Tw> tw((size_t)nm * kTwLen), itn((size_t)nm * kRootLen);
+  std::vector<Powers> pws;
   for (uint32_t m = 0; m < nm; m++) {
     const uint64_t q = ctx->mods[m];
     ModConst &c = mc[m];
@@ -340,126 +421,157 @@ int build_context(const hck_params *prm, int device, void *stream, hck_context *
     c.r2 = h_mulmod(c.r64, c.r64, q);
     c.one_shoup = h_shoup(1, q);
     c.nq = 0 - q;
-    const uint64_t psi = primitive_2n_root(q, n), ipsi = h_invmod(psi, q);
-    pw[0] = ipw[0] = 1;
-    for (uint32_t i = 1; i < n; i++) {
-      pw[i] = h_mulmod(pw[i - 1], psi, q);
-      ipw[i] = h_mulmod(ipw[i - 1], ipsi, q);
-    }
-    for (uint32_t k = 0; k < n; k++) {
-      const uint32_t b = bit_reverse(k, ctx->log_n);
-      tw[(size_t)m * n + k] = pw[b];
-      tws[(size_t)m * n + k] = h_shoup(pw[b], q);
-      itw[(size_t)m * n + k] = ipw[b];
-      itws[(size_t)m * n + k] = h_shoup(ipw[b], q);
-    }
-    twist_rows(pw, ipw, q, ctx->log_n, log_a, (size_t)m * n, ttw, ttws, ittw, ittws);
+    c.qd = h_float_modulus(q) ? (double)q : 0.0;
+    c.qid = h_float_modulus(q) ? 1.0 / (double)q : 0.0;
+    pws.emplace_back(q, n);
+    for (uint32_t k = 0; k < (uint32_t)kTwLen; k++)
+      tw[(size_t)m * kTwLen + k] = h_tw(pws[m].pos(bit_reverse(k, ctx->log_n)), q);
+    for (uint32_t k = 0; k < (uint32_t)kRootLen; k++)
+      itn[(size_t)m * kRootLen + k] = h_tw(pws[m].neg((uint64_t)k * (n / kRootLen)), q);
   }
 
   // ModUp tables: for each level l and digit j with limbs D = [lo, hi),
-  // scale_i = N^-1 (Q_D / q_i)^-1 mod q_i and conv[a][m] = (Q_D / q_(lo+a)) 2^64 mod m.
+  // row factors N^-1 (Q_D / q_i)^-1 psi^(-R2 r) mod q_i and the constants
+  // Q_D / q_(lo+a) mod m.
   const uint32_t A = ctx->alpha;
-  std::vector<uint64_t> up_conv((size_t)L * ctx->dnum * A * nm, 0);
-  ctx->up_scale.assign(L, std::vector<uint64_t>(L, 0));
+  const uint32_t r1 = 1u << ((ctx->log_n + 1) / 2), r2 = n / r1;
+  auto row_factors = [&](uint32_t m, uint64_t scale, Tw *out) {
+    for (uint32_t r = 0; r < r1; r++)
+      out[r] = h_tw(h_mulmod(scale, pws[m].neg((uint64_t)r2 * r), ctx->mods[m]), ctx->mods[m]);
+  };
+  std::vector<ConvC> up_conv((size_t)L * ctx->dnum * (A + 1) * nm, ConvC{});
+  std::vector<Tw> up_rows((size_t)L * L * r1, Tw{0, 0});
+  ctx->conv_f = true;
   for (uint32_t l = 0; l < L; l++) {
     for (uint32_t j = 0; j < ctx->dnum; j++) {
       const uint32_t lo = j * A;
       if (lo > l) break;
       const uint32_t hi = std::min(lo + A, l + 1);
-      for (uint32_t a = 0; a < hi - lo; a++) {
-        const uint32_t i = lo + a;
-        uint64_t hat_i = 1;
+      const std::vector<uint64_t> src(ctx->mods.begin() + lo, ctx->mods.begin() + hi);
+      auto hat = [&](uint32_t i, uint64_t t) {  // Q_D / q_i mod t
+        uint64_t h = 1;
         for (uint32_t k = lo; k < hi; k++)
-          if (k != i) hat_i = h_mulmod(hat_i, ctx->mods[k] % ctx->mods[i], ctx->mods[i]);
-        ctx->up_scale[l][i] =
-            h_mulmod(h_invmod(hat_i, ctx->mods[i]), mc[i].ninv, ctx->mods[i]);
-        for (uint32_t m = 0; m < nm; m++) {
-          const uint64_t t = ctx->mods[m];
-          uint64_t hat_t = 1;
-          for (uint32_t k = lo; k < hi; k++)
-            if (k != i) hat_t = h_mulmod(hat_t, ctx->mods[k] % t, t);
-          up_conv[(((size_t)l * ctx->dnum + j) * A + a) * nm + m] = h_mulmod(hat_t, mc[m].r64, t);
-        }
+          if (k != i) h = h_mulmod(h, ctx->mods[k] % t, t);
+        return h % t;
+      };
+      for (uint32_t i = lo; i < hi; i++) {
+        const uint64_t q = ctx->mods[i];
+        row_factors(i, h_mulmod(h_invmod(hat(i, q), q), mc[i].ninv, q),
+                    &up_rows[((size_t)l * L + i) * r1]);
+      }
+      for (uint32_t m = 0; m < nm; m++) {
+        const uint64_t t = ctx->mods[m];
+        const bool ok = conv_constants(
+            src, t, [&](size_t a) { return hat(lo + (uint32_t)a, t); },
+            &up_conv[((size_t)l * ctx->dnum + j) * (A + 1) * nm + m], nm);
+        // (a digit is not converted to its own limbs)
+        if (m < lo || m >= hi) ctx->conv_f = ctx->conv_f && ok;
       }
     }
   }
 
   // ModDown tables over P = prod p_k, with the rounding addend h = (P-1)/2.
-  std::vector<uint64_t> down_conv((size_t)K * nm, 0);
-  ctx->down_scale.assign(K, 0);
-  ctx->down_add.assign(K, 0);
-  for (uint32_t k = 0; k < K; k++) {
-    const uint32_t mk = L + k;
-    const uint64_t pk = ctx->mods[mk];
-    uint64_t hat = 1;
+  std::vector<ConvC> down_conv((size_t)(K + 1) * nm, ConvC{});
+  std::vector<Tw> down_rows((size_t)K * r1);
+  std::vector<uint64_t> down_add(K);
+  const std::vector<uint64_t> specials(ctx->mods.begin() + L, ctx->mods.end());
+  auto down_hat = [&](uint32_t k, uint64_t t) {  // P / p_k mod t
+    uint64_t h = 1;
     for (uint32_t r = 0; r < K; r++)
-      if (r != k) hat = h_mulmod(hat, ctx->mods[L + r] % pk, pk);
-    const uint64_t hat_inv = h_invmod(hat, pk);
-    ctx->down_scale[k] = h_mulmod(hat_inv, mc[mk].ninv, pk);
+      if (r != k) h = h_mulmod(h, specials[r] % t, t);
+    return h % t;
+  };
+  for (uint32_t k = 0; k < K; k++) {
+    const uint64_t pk = specials[k];
+    const uint64_t hat_inv = h_invmod(down_hat(k, pk), pk);
+    row_factors(L + k, h_mulmod(hat_inv, mc[L + k].ninv, pk), &down_rows[(size_t)k * r1]);
     // (P-1)/2 mod p_k = -2^-1 mod p_k
-    const uint64_t h = pk - h_invmod(2, pk);
-    ctx->down_add[k] = h_mulmod(h, hat_inv, pk);
-    for (uint32_t m = 0; m < L; m++) {
-      const uint64_t t = ctx->mods[m];
-      uint64_t hat_t = 1;
-      for (uint32_t r = 0; r < K; r++)
-        if (r != k) hat_t = h_mulmod(hat_t, ctx->mods[L + r] % t, t);
-      down_conv[(size_t)k * nm + m] = h_mulmod(hat_t, mc[m].r64, t);
+    down_add[k] = h_mulmod(pk - h_invmod(2, pk), hat_inv, pk);
+  }
+  for (uint32_t m = 0; m < L; m++) {
+    const uint64_t t = ctx->mods[m];
+    const bool ok = conv_constants(
+        specials, t, [&](size_t k) { return down_hat((uint32_t)k, t); }, &down_conv[m], nm);
+    ctx->conv_f = ctx->conv_f && ok;
+  }
+
+  // targets per workgroup of the basis conversions: single, and pairs of
+  // consecutive targets of one arithmetic
+  std::vector<ConvGroup> groups;
+  auto group_targets = [&](const std::vector<ConvGroup> &one, bool pairs) {
+    const std::pair<uint32_t, uint32_t> none((uint32_t)groups.size(), 0);
+    auto range = none;
+    for (size_t i = 0; i < one.size(); i++) {
+      ConvGroup g = one[i];
+      if (pairs && i + 1 < one.size() && one[i + 1].digit == g.digit &&
+          h_float_modulus(ctx->mods[g.mod[0]]) ==
+              h_float_modulus(ctx->mods[one[i + 1].mod[0]])) {
+        g.row[1] = one[i + 1].row[0];
+        g.mod[1] = one[i + 1].mod[0];
+        g.n = 2;
+        i++;
+      }
+      groups.push_back(g);
+      range.second++;
+    }
+    return range;
+  };
+  for (uint32_t l = 0; l < L; l++) {
+    std::vector<ConvGroup> up, down;
+    const uint32_t nq = l + 1, ne = nq + K;
+    for (uint32_t j = 0; j * A < nq; j++)
+      for (uint32_t t = 0; t < ne; t++) {
+        if (t >= j * A && t < std::min((j + 1) * A, nq)) continue;
+        const uint8_t m = (uint8_t)(t < nq ? t : L + (t - nq));
+        const uint16_t row = (uint16_t)(L + j * ne + t);
+        up.push_back(ConvGroup{{row, row}, {m, m}, (uint8_t)j, 1});
+      }
+    for (uint32_t t = 0; t < nq; t++)
+      down.push_back(ConvGroup{{0, 0}, {(uint8_t)t, (uint8_t)t}, 0, 1});
+    for (int pairs = 0; pairs < 2; pairs++) {
+      ctx->groups[pairs].push_back(group_targets(up, pairs));
+      ctx->down_groups[pairs].push_back(group_targets(down, pairs));
     }
   }
-  ctx->down_hneg.assign(L, 0);
-  ctx->pinv.assign(L, 0);
+  std::vector<uint64_t> down_hneg(L);
+  std::vector<Tw> pinv(L), rescale((size_t)L * L, Tw{0, 0});
   for (uint32_t i = 0; i < L; i++) {
     const uint64_t q = ctx->mods[i];
     uint64_t pm = 1;
     for (uint32_t k = 0; k < K; k++) pm = h_mulmod(pm, ctx->mods[L + k] % q, q);
-    ctx->pinv[i] = h_invmod(pm, q);
+    pinv[i] = h_tw(h_invmod(pm, q), q);
     // (P-1)/2 mod q = (P mod q - 1) 2^-1 mod q; stored negated
     const uint64_t h = h_mulmod((pm + q - 1) % q, h_invmod(2, q), q);
-    ctx->down_hneg[i] = h == 0 ? 0 : q - h;
+    down_hneg[i] = h == 0 ? 0 : q - h;
   }
-  ctx->rescale_inv.assign(L, std::vector<uint64_t>(L, 0));
   for (uint32_t l = 1; l < L; l++)
     for (uint32_t i = 0; i < l; i++)
-      ctx->rescale_inv[l][i] = h_invmod(ctx->mods[l] % ctx->mods[i], ctx->mods[i]);
+      rescale[(size_t)l * L + i] =
+          h_tw(h_invmod(ctx->mods[l] % ctx->mods[i], ctx->mods[i]), ctx->mods[i]);
 
   // upload
-  auto up = [&](uint64_t **dst, const void *src, size_t bytes) -> int {
-    if (hipMalloc((void **)dst, bytes) != hipSuccess) {
-      (void)hipGetLastError();
-      return set_error(HCK_ENOMEM, "table allocation failed");
-    }
-    if (hipMemcpy(*dst, src, bytes, hipMemcpyHostToDevice) != hipSuccess)
-      return check_hip(ctx, hipGetLastError(), "table upload");
-    return HCK_OK;
+  auto up = [&](auto **dst, const auto &v) {
+    return upload_table(ctx, (void **)dst, v.data(), v.size() * sizeof(v[0]));
   };
-  const size_t tb = (size_t)nm * n * 8;
-  if ((rc = up((uint64_t **)&ctx->d_mod, mc.data(), nm * sizeof(ModConst))) ||
-      (rc = up(&ctx->d_tw, tw.data(), tb)) || (rc = up(&ctx->d_tw_shoup, tws.data(), tb)) ||
-      (rc = up(&ctx->d_itw, itw.data(), tb)) || (rc = up(&ctx->d_itw_shoup, itws.data(), tb)) ||
-      (rc = up(&ctx->d_ttw, ttw.data(), tb)) || (rc = up(&ctx->d_ttw_shoup, ttws.data(), tb)) ||
-      (rc = up(&ctx->d_ittw, ittw.data(), tb)) ||
-      (rc = up(&ctx->d_ittw_shoup, ittws.data(), tb)) ||
-      (rc = up(&ctx->d_up_conv, up_conv.data(), up_conv.size() * 8)) ||
-      (rc = up(&ctx->d_down_conv, down_conv.data(), down_conv.size() * 8)) ||
-      (rc = up(&ctx->d_down_hneg, ctx->down_hneg.data(), ctx->down_hneg.size() * 8))) {
+  if ((rc = up(&ctx->d_mod, mc)) || (rc = up(&ctx->d_tw, tw)) || (rc = up(&ctx->d_itn, itn)) ||
+      (rc = make_split(ctx, pws, (int)(ctx->log_n + 1) / 2, &ctx->split[0])) ||
+      (rc = up(&ctx->d_up_conv, up_conv)) || (rc = up(&ctx->d_up_rows, up_rows)) ||
+      (rc = up(&ctx->d_down_conv, down_conv)) || (rc = up(&ctx->d_down_rows, down_rows)) ||
+      (rc = up(&ctx->d_down_add, down_add)) || (rc = up(&ctx->d_down_hneg, down_hneg)) ||
+      (rc = up(&ctx->d_pinv, pinv)) || (rc = up(&ctx->d_rescale, rescale)) ||
+      (rc = up(&ctx->d_groups, groups))) {
     hck_context_destroy(ctx);
     return rc;
   }
-  ctx->def_twist[0] = ctx->d_ttw;
-  ctx->def_twist[1] = ctx->d_ttw_shoup;
-  ctx->def_twist[2] = ctx->d_ittw;
-  ctx->def_twist[3] = ctx->d_ittw_shoup;
   *out = ctx;
   return HCK_OK;
 }
 
-const uint64_t *const *split_twists(const hck_context *ctx, int a) {
+const hck_context::Split *split_tables(const hck_context *ctx, int a) {
   const int a0 = (ctx->log_n + 1) / 2;
-  if (a == a0) return ctx->def_twist;
-  if (a != a0 - 1 && a != a0 + 1) return nullptr;
-  const auto &t = ctx->alt_twist[a == a0 + 1];
-  return t[0] ? t : nullptr;
+  if (a < a0 - 1 || a > a0 + 1) return nullptr;
+  const hck_context::Split &sp = ctx->split[a == a0 ? 0 : a < a0 ? 1 : 2];
+  return sp.twist ? &sp : nullptr;
 }
 
 int set_ntt_split(hck_context *ctx, int a) {
@@ -472,34 +584,12 @@ int set_ntt_split(hck_context *ctx, int a) {
     return set_error(HCK_EINVAL, "NTT split " + std::to_string(a) + " not available at log N " +
                                      std::to_string(ctx->log_n));
   if (ctx->capturing) return set_error(HCK_EINVAL, "NTT split change during graph capture");
-  auto &t = ctx->alt_twist[a == a0 + 1];
-  if (!t[0]) {
-    const uint32_t nm = ctx->L + ctx->K;
-    const size_t n = ctx->n;
-    std::vector<uint64_t> ttw(nm * n), ttws(nm * n), ittw(nm * n), ittws(nm * n), pw(n), ipw(n);
-    for (uint32_t m = 0; m < nm; m++) {
-      const uint64_t q = ctx->mods[m];
-      const uint64_t psi = primitive_2n_root(q, n), ipsi = h_invmod(psi, q);
-      pw[0] = ipw[0] = 1;
-      for (size_t i = 1; i < n; i++) {
-        pw[i] = h_mulmod(pw[i - 1], psi, q);
-        ipw[i] = h_mulmod(ipw[i - 1], ipsi, q);
-      }
-      twist_rows(pw, ipw, q, ctx->log_n, a, (size_t)m * n, ttw, ttws, ittw, ittws);
-    }
-    const std::vector<uint64_t> *src[4] = {&ttw, &ttws, &ittw, &ittws};
-    uint64_t *dev[4] = {};
-    for (int k = 0; k < 4; k++) {
-      hipError_t e = hipMalloc((void **)&dev[k], nm * n * 8);
-      if (e == hipSuccess) e = hipMemcpy(dev[k], src[k]->data(), nm * n * 8, hipMemcpyHostToDevice);
-      if (e != hipSuccess) {
-        for (uint64_t *p : dev)
-          if (p) (void)hipFree(p);
-        (void)hipGetLastError();
-        return set_error(HCK_ENOMEM, "NTT split tables: allocation or upload failed");
-      }
-    }
-    for (int k = 0; k < 4; k++) t[k] = dev[k];
+  hck_context::Split &sp = ctx->split[a < a0 ? 1 : 2];
+  if (!sp.twist) {
+    std::vector<Powers> pws;
+    for (uint64_t q : ctx->mods) pws.emplace_back(q, ctx->n);
+    const int rc = make_split(ctx, pws, a, &sp);
+    if (rc) return rc;
   }
   ctx->ntt_a = (uint8_t)a;
   return HCK_OK;
@@ -538,14 +628,13 @@ void destroy_context(hck_context *ctx) {
   ctx->ct_pool.clear();
   if (ctx->stream) (void)hipStreamSynchronize(ctx->stream);
   else (void)hipDeviceSynchronize();
-  for (void *p : {(void *)ctx->d_mod, (void *)ctx->d_tw, (void *)ctx->d_tw_shoup,
-                  (void *)ctx->d_itw, (void *)ctx->d_itw_shoup, (void *)ctx->d_ttw,
-                  (void *)ctx->d_ttw_shoup, (void *)ctx->d_ittw, (void *)ctx->d_ittw_shoup,
-                  (void *)ctx->d_up_conv,
-                  (void *)ctx->d_down_conv, (void *)ctx->d_down_hneg})
+  for (void *p : {(void *)ctx->d_mod, (void *)ctx->d_tw, (void *)ctx->d_itn,
+                  (void *)ctx->d_up_conv, (void *)ctx->d_up_rows, (void *)ctx->d_down_conv,
+                  (void *)ctx->d_down_rows, (void *)ctx->d_down_add, (void *)ctx->d_down_hneg,
+                  (void *)ctx->d_pinv, (void *)ctx->d_rescale, (void *)ctx->d_groups})
     if (p) (void)hipFree(p);
-  for (auto &t : ctx->alt_twist)
-    for (uint64_t *p : t)
+  for (auto &sp : ctx->split)
+    for (void *p : {(void *)sp.twist, (void *)sp.itwist, (void *)sp.rows})
       if (p) (void)hipFree(p);
   for (auto &t : ctx->pending) {
     (void)hipEventDestroy(t.start);

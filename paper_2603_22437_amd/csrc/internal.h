@@ -16,6 +16,8 @@ namespace hck {
 
 constexpr int kMaxLimbs = HCK_MAX_LIMBS;
 constexpr int kMaxRows = 256;  // rows of one batched launch (e.g. every extended digit)
+constexpr int kTwLen = 1024;   // forward twiddles kept per modulus (ntt_core.h)
+constexpr int kRootLen = 512;  // inverse roots kept per modulus: half of a 2^10-point circle
 constexpr int kMaxBatch = 32;  // key switches run together in one sequence of launches
 
 // Per-modulus constants, indexed by the modulus index of the full chain
@@ -30,6 +32,27 @@ struct ModConst {
   uint64_t r2;          // 2^128 mod q (Montgomery fix-up of a plain product)
   uint64_t one_shoup;   // floor(2^64 / q): Shoup companion of 1 (reduction of any word)
   uint64_t nq;          // 2^64 - q
+  // q and 1/q as doubles where the transforms run on doubles, else 0
+  double qd, qid;
+};
+
+// One constant c of a basis conversion, from source limb a to a target
+// modulus (ks_fused.hip): in Montgomery form for integer targets; for targets
+// on doubles its centred value in 25-bit halves c = c1 2^25 + c0, cs = c0 + c1,
+// and, where the source's prime is not in the floating-point range, the halves
+// of c 2^50 mod t (e0 and es = e0 + e1).  The row after the last source holds
+// in c0 the constant that undoes the centring of the sources.
+struct alignas(16) ConvC {
+  uint64_t w;
+  double c0, c1, cs, e0, es;
+};
+
+// Targets that one workgroup of a basis conversion converts together: ext rows (from
+// the slot's start) and moduli, of one arithmetic.
+struct ConvGroup {
+  uint16_t row[2];
+  uint8_t mod[2];
+  uint8_t digit, n;
 };
 
 // Which rows of a [row][N] buffer a launch processes (blockIdx.y indexes the
@@ -59,27 +82,31 @@ struct hck_context {
 
   // device tables
   hck::ModConst *d_mod = nullptr;    // [L+K]
-  uint64_t *d_tw = nullptr;          // [L+K][N] psi^brv(k)
-  uint64_t *d_tw_shoup = nullptr;
-  uint64_t *d_itw = nullptr;         // [L+K][N] psi^-brv(k)
-  uint64_t *d_itw_shoup = nullptr;
-  uint64_t *d_ttw = nullptr;         // [L+K][N] contiguous-pass twist beta_g^i (ntt_core.h)
-  uint64_t *d_ttw_shoup = nullptr;
-  uint64_t *d_ittw = nullptr;        // [L+K][N] inverse twist beta_g^-i
-  uint64_t *d_ittw_shoup = nullptr;
-  // basis conversion matrices (Montgomery form, per (level, digit) or ModDown)
-  uint64_t *d_up_conv = nullptr;     // [L][dnum][alpha][L+K]
-  uint64_t *d_down_conv = nullptr;   // [K][L+K] (columns < L used)
+  hck::Tw *d_tw = nullptr;       // [L+K][kTwLen] psi^brv(k)
+  hck::Tw *d_itn = nullptr;      // [L+K][kRootLen] omega^-j, omega = psi^(N / kRootLen)
+  // per split of the transforms (hck_split below): default, one below, one above
+  struct Split {
+    hck::Tw *twist = nullptr;    // [L+K][N] contiguous-pass twist (ntt_core.h)
+    hck::Tw *itwist = nullptr;   // [L+K][N] its inverse
+    hck::Tw *rows = nullptr;     // [L+K][R1] row factors of the inverse: N^-1 psi^(-R2 i)
+  } split[3];
+  // row factors of the key switch's scaled inverse passes (default split)
+  hck::Tw *d_up_rows = nullptr;    // [L levels][L][R1]: (Q_j / q_i)^-1 included
+  hck::Tw *d_down_rows = nullptr;  // [K][R1]: (P / p_k)^-1 included
+  uint64_t *d_down_add = nullptr;  // [K]: ((P-1)/2 mod p_k) (P/p_k)^-1 mod p_k
+  // basis conversion constants, per (level, digit) or ModDown
+  hck::ConvC *d_up_conv = nullptr;   // [L][dnum][alpha + 1][L+K]
+  hck::ConvC *d_down_conv = nullptr; // [K + 1][L+K] (columns < L used)
   uint64_t *d_down_hneg = nullptr;   // [L]: -(P-1)/2 mod q_i
-
-  // host copies of per-row scale factors
-  // up_scale[level][i]: N^-1 (Q'_j / q_i)^-1 mod q_i, digit j of limb i at that level
-  std::vector<std::vector<uint64_t>> up_scale;
-  std::vector<uint64_t> down_scale;   // [K]: N^-1 (P/p_k)^-1 mod p_k
-  std::vector<uint64_t> down_add;     // [K]: ((P-1)/2 mod p_k) (P/p_k)^-1 mod p_k
-  std::vector<uint64_t> down_hneg;    // [L]: -(P-1)/2 mod q_i
-  std::vector<uint64_t> pinv;         // [L]: P^-1 mod q_i
-  std::vector<std::vector<uint64_t>> rescale_inv;  // [l][i<l]: q_l^-1 mod q_i
+  hck::Tw *d_pinv = nullptr;         // [L]: P^-1 mod q_i
+  hck::Tw *d_rescale = nullptr;      // [L][L]: q_l^-1 mod q_i (i < l)
+  // ModUp targets grouped one or two to a workgroup, per level
+  hck::ConvGroup *d_groups = nullptr;
+  std::vector<std::pair<uint32_t, uint32_t>> groups[2];       // [pairs?][level]: (first, count)
+  std::vector<std::pair<uint32_t, uint32_t>> down_groups[2];  // the same of the ModDown (row unused)
+  // targets on doubles are converted in doubles: every sum of products of
+  // halves stays exact for this context's constants
+  bool conv_f = false;
 
   // key-switch workspace (device)
   uint64_t *ws = nullptr;
@@ -93,17 +120,13 @@ struct hck_context {
   // stream-ordered hipMallocAsync / hipFreeAsync; live_allocs counts the
   // buffers dev_alloc handed out and dev_free has not yet returned
   // split of the plain full NTTs (log2 of the strided radix R1; 0: the
-  // default (log N + 1) / 2), chosen by hck_autotune_ntt; alt_twist[0] and
-  // [1] are the contiguous pass's twist tables (forward, its Shoup
-  // companions, inverse, its companions) of the splits one below and one
-  // above the default, built when first chosen and kept until the context is
-  // destroyed (recorded graphs may read them)
+  // default (log N + 1) / 2), chosen by hck_autotune_ntt; the tables of the
+  // splits one below and one above the default are built when first chosen
+  // and kept until the context is destroyed (recorded graphs may read them)
   uint8_t ntt_a = 0;
   // every modulus below 2^60: the basis conversions sum products of 30-bit
   // halves in carry-free 64-bit columns
   bool bconv30 = false;
-  uint64_t *alt_twist[2][4] = {};
-  uint64_t *def_twist[4] = {};
   // key switches per launch sequence at each level, chosen by the autotuner
   // (hck_autotune_keyswitch) or set by the caller; 0: the built-in rule
   uint8_t ks_cap[HCK_MAX_LIMBS] = {};
@@ -214,7 +237,8 @@ struct hck_public_key {
 
 struct hck_switch_key {
   hck_context *ctx = nullptr;
-  uint64_t *data = nullptr;  // [dnum][2][L+K][N] evaluation domain, Montgomery form
+  // [dnum][2][L+K][N] evaluation domain, in the key switch's form (launch_key_form)
+  uint64_t *data = nullptr;
 };
 
 struct hck_galois_keys {
@@ -288,30 +312,58 @@ int timing_collect(hck_context *ctx);
 // forward NTT, in place, rows of `buf` listed in map; input fully reduced,
 // output fully reduced
 int ntt_forward(hck_context *ctx, uint64_t *buf, const LimbMap &map);
-// inverse NTT, in place; output x * scale.w + scale.add (fully reduced); when
-// scale is null, multiplies by N^-1 only
-int ntt_inverse(hck_context *ctx, uint64_t *buf, const LimbMap &map, const RowScale *scale);
-// out-of-place variants: the first pass reads src, both passes write dst
-int ntt_forward_oop(hck_context *ctx, uint64_t *dst, const uint64_t *src, const LimbMap &map);
-int ntt_inverse_oop(hck_context *ctx, uint64_t *dst, const uint64_t *src, const LimbMap &map,
-                    const RowScale *scale);
-// one pass (strided or contiguous, forward or inverse) in place; an inverse
-// strided pass with `scale` uses entry (row list index mod period) (period 0:
-// the list index itself)
+// inverse NTT, in place, times N^-1; input and output fully reduced
+int ntt_inverse(hck_context *ctx, uint64_t *buf, const LimbMap &map);
 // Rescale of polys polynomials at `level` (in and out strided by the
 // polynomial stride, out may be in): last holds each polynomial's dropped limb
 // in coefficient form ([0, q_level)), tmp has room for polys x level limbs.
 int rescale_fused(hck_context *ctx, uint64_t *out, const uint64_t *in, const uint64_t *last,
                   uint64_t *tmp, uint32_t level, uint32_t polys);
 // whether the plain transforms of a ring can run on split a (the default or
-// one step either side), and the twist tables of split a (null: not built)
+// one step either side), and the tables of split a (null: not built)
 bool ntt_split_available(uint32_t log_n, int a);
-const uint64_t *const *split_twists(const hck_context *ctx, int a);
+const hck_context::Split *split_tables(const hck_context *ctx, int a);
 // selects the split of the plain full transforms (0: the default), building
-// its twist tables on first use
+// its tables on first use
 int set_ntt_split(hck_context *ctx, int a);
+// The scaled inverse strided pass of key switching: row list entry k is
+// multiplied by row factors k mod period of `rows` ([period][R1]), then
+// add[k mod period] is added where add is given.  canonical: the rows hold
+// fully reduced words (else the contiguous pass's output).
+struct RowFactors {
+  const Tw *rows;
+  const uint64_t *add;
+  uint32_t period;
+  bool canonical;
+};
+// one pass (strided or contiguous, forward or inverse) in place, default split
 int ntt_pass(hck_context *ctx, uint64_t *buf, const LimbMap &map, bool inverse, bool strided,
-             const RowScale *scale, int period = 0);
+             const RowFactors *scale);
+// The transforms and key switching of one ring degree (ntt.hip, ks_fused.hip;
+// one object per ring, dispatched by rings.cpp)
+template <int LOGN>
+struct NttRing {
+  static bool split_available(int a);
+  static int ntt_full(hck_context *ctx, uint64_t *buf, const LimbMap &map, bool inverse);
+  static int ntt_pass(hck_context *ctx, uint64_t *buf, const LimbMap &map, bool inverse,
+                      bool strided, const RowFactors *scale);
+  static int rescale(hck_context *ctx, uint64_t *out, const uint64_t *in, const uint64_t *last,
+                     uint64_t *tmp, uint32_t level, uint32_t polys);
+};
+struct KsBatch;
+template <int LOGN>
+struct KsRing {
+  static int run(hck_context *ctx, const KsBatch &kb, uint32_t level, uint64_t *ws);
+  static int hoisted(hck_context *ctx, const uint64_t *c0, const uint64_t *c1, uint32_t level,
+                     const uint32_t *galois, const hck_switch_key *const *keys, uint32_t n,
+                     uint64_t *const *out0, uint64_t *const *out1);
+  static int pq(hck_context *ctx, const KsBatch &kb, uint32_t level, uint64_t *const *pq,
+                const bool *first);
+  static int md(hck_context *ctx, const KsBatch &kb, uint32_t level, const uint64_t *const *pq);
+};
+// switch-key rows: evaluation + Montgomery form <-> the key switch's form
+// (centred doubles for moduli on doubles, Montgomery form for the others)
+int launch_key_form(hck_context *ctx, uint64_t *buf, const LimbMap &map, bool to);
 
 int launch_copy(hck_context *ctx, uint64_t *dst, const uint64_t *src, size_t words);
 // out[r] = a[r] (+|-) b[r] for rows in map; op 0 add, 1 sub, 2 negate a
@@ -342,13 +394,6 @@ int launch_automorphism(hck_context *ctx, uint64_t *out, const uint64_t *in, siz
                         uint32_t polys, const LimbMap &map, uint32_t galois);
 // small signed integers -> residues for rows in map
 int launch_embed_small(hck_context *ctx, uint64_t *out, const int32_t *small, const LimbMap &map);
-// rescale: lift the coefficient-domain last limbs last[p] (p < polys) into
-// out[p][0..level-1]
-int launch_rescale_lift(hck_context *ctx, uint64_t *out, const uint64_t *last, uint32_t level,
-                        uint32_t polys);
-// rescale tail: out_p,i = (c_p,i - t[p][i]) q_l^-1 mod q_i (poly stride L N)
-int launch_rescale_tail(hck_context *ctx, uint64_t *out, const uint64_t *c, const uint64_t *t,
-                        uint32_t level, uint32_t polys);
 // out[r] += REDC(in[r] c_r) for rows in map, c_r = sc.w[list index]
 int launch_scalar_mac(hck_context *ctx, uint64_t *out, const uint64_t *in, const LimbMap &map,
                       const RowScale &sc);

@@ -132,6 +132,33 @@ __global__ __launch_bounds__(kThreads) void k_to_mont(uint64_t *buf, LimbMap map
   }
 }
 
+// switch-key words: evaluation form <-> centred doubles (moduli on doubles)
+// or Montgomery form
+__global__ __launch_bounds__(kThreads) void k_key_form(uint64_t *buf, LimbMap map,
+                                                       const ModConst *__restrict__ mc, int n,
+                                                       int to) {
+  const int i = blockIdx.x * kThreads + threadIdx.x;
+  const size_t off = (size_t)map.row[blockIdx.y] * n + i;
+  const ModConst m = mc[map.mod[blockIdx.y]];
+  const uint64_t x = buf[off];
+  if (m.qd != 0.0) {
+    if (to) {
+      const double d = (double)(x > m.q / 2 ? (int64_t)x - (int64_t)m.q : (int64_t)x);
+      buf[off] = (uint64_t)__double_as_longlong(d);
+    } else {
+      const int64_t v = (int64_t)__longlong_as_double((long long)x);
+      buf[off] = v < 0 ? (uint64_t)(v + (int64_t)m.q) : (uint64_t)v;
+    }
+  } else if (to) {
+    buf[off] = shoup(x, m.r64, m.r64_shoup, m.q);
+  } else {
+    u128 t;
+    t.lo = x;
+    t.hi = 0;
+    buf[off] = redc(t, m.q, m.qinv);
+  }
+}
+
 // (a0, a1) x (b0, b1) -> (a0 b0, a0 b1 + a1 b0, a1 b1); plain operands, so
 // each REDC result (x 2^-64) is brought back by a REDC with 2^128 mod q.
 __global__ __launch_bounds__(kThreads) void k_tensor(uint64_t *out, const uint64_t *a,
@@ -309,6 +336,17 @@ int launch_to_mont(hck_context *ctx, uint64_t *buf, const LimbMap &map, bool to)
   timing_begin(ctx, "mont", grid_rows(ctx, map.n), 16.0 * ctx->n * map.n, (double)ctx->n * map.n);
   k_to_mont<<<grid_rows(ctx, map.n), kThreads, 0, ctx->stream>>>(buf, map, ctx->d_mod, ctx->n,
                                                                   to ? 1 : 0);
+  timing_end(ctx);
+  HCK_HIP(ctx, hipGetLastError());
+  return HCK_OK;
+}
+
+int launch_key_form(hck_context *ctx, uint64_t *buf, const LimbMap &map, bool to) {
+  if (map.n == 0) return HCK_OK;
+  timing_begin(ctx, "key_form", grid_rows(ctx, map.n), 16.0 * ctx->n * map.n,
+               (double)ctx->n * map.n);
+  k_key_form<<<grid_rows(ctx, map.n), kThreads, 0, ctx->stream>>>(buf, map, ctx->d_mod, ctx->n,
+                                                                   to ? 1 : 0);
   timing_end(ctx);
   HCK_HIP(ctx, hipGetLastError());
   return HCK_OK;

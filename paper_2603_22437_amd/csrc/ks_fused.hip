@@ -7,24 +7,29 @@
 // rotation never materializes phi_g(c):
 //   K1  inverse contiguous pass of phi_g(d) over Q_l -> y          (gather;
 //       also the copy of c0 for an output that aliases its input)
-//   K2  inverse strided pass, times N^-1 (Q_j / q_i)^-1 per limb    (digit scale)
+//   K2  inverse strided pass, row factors with (Q_j / q_i)^-1      (digit scale)
 //   K3  ModUp: per digit j and target limb t not in D_j, the fast basis
 //       conversion of y's digit limbs computed at load time, then the
 //       forward strided pass -> ext[j][t]
-//   K4  per extended limb t: forward contiguous pass of every digit's ext
-//       (or phi_g(d) itself on the digit's own limbs), then
-//       acc_{0,1}[t] = sum_j d~_j[t] swk_j[t] (keys in Montgomery form); slots
-//       that share a key re-read its tiles from cache; on the P limbs the
-//       inverse contiguous pass of K5 follows in the same kernel
-//   K5  inverse passes of acc's P limbs, times N^-1 (P/p_k)^-1, plus
-//       ((P-1)/2) (P/p_k)^-1 (the rounding term of ModDown)
+//   K4  special limbs t: forward contiguous pass of every digit's ext, then
+//       acc_{0,1}[t] = sum_j d~_j[t] swk_j[t], then the inverse contiguous
+//       pass of K5
+//   K5  inverse strided pass of acc's P limbs, row factors with (P/p_k)^-1,
+//       plus ((P-1)/2) (P/p_k)^-1 (the rounding term of ModDown)
 //   K6  ModDown conversion P -> q_i (minus (P-1)/2) at load time, then the
 //       forward strided pass -> conv
-//   K7  forward contiguous pass of conv, then
-//       out_i = (acc_i - conv_i) P^-1 (+ phi_g(addend)_i)
+//   K7  Q limbs: the forward passes and key products of K4 (phi_g(d) itself on
+//       the digit's own limbs), kept in registers, then the forward contiguous
+//       pass of conv and out_i = (acc_i - conv_i) P^-1 (+ phi_g(addend)_i)
+// Switching the special limbs first keeps the Q limbs' accumulators out of
+// memory (2 (l + 1) rows a switch, written once and read once).
 //
 // Workspace: batch slot b occupies rows [b R, (b+1) R) of ws_ks (R rows of N
-// words): y [L] | ext [dnum][L+K] | acc [2][L+K] | conv [2][L].
+// words): y [L] | ext [dnum][L+K] | acc [2][L+K] | conv [2][L].  Rows between
+// two passes hold words in their modulus' own arithmetic; y, the special rows
+// after K5 and the accumulators of the paths that store them are fully
+// reduced integers.
+// Compiled once per ring, with HCK_LOGN its log2 N (build.py).
 #include <algorithm>
 
 #include "ntt_core.h"
@@ -33,11 +38,9 @@ namespace hck {
 
 namespace {
 
-struct KsGeom;
-// the largest kernel argument list (ModDown tail: batch table, row scales,
-// geometry, pointers) stays within the 4 KiB a kernel can take
-static_assert(sizeof(KsBatch) + sizeof(RowScale) + 128 + 64 <= 4096,
-              "kernel arguments beyond 4 KiB");
+// the largest kernel argument list (batch table, geometry, pointers) stays
+// within the 4 KiB a kernel can take
+static_assert(sizeof(KsBatch) + 256 <= 4096, "kernel arguments beyond 4 KiB");
 
 struct KsGeom {
   uint32_t level, nq, ne, L, K, dnum, alpha, nm;
@@ -45,37 +48,26 @@ struct KsGeom {
   uint32_t off_ext, off_acc, off_conv;      // row offsets inside a slot
 };
 
-// One launch of the ModUp: entry k converts digit digit[k] (source rows from
-// src[k]) into target modulus mod[k] (output row row[k]) and, where row2[k] is
-// not kNoRow, into mod2[k] (row2[k]) from the same reads of the sources.
-constexpr uint16_t kNoRow = 0xffff;
 // workgroups (at one target each) from which the basis conversions pair
 // targets: halved, they still fill the chip twice over at the paired kernel's
 // occupancy (about 3 workgroups of 256 threads per CU)
 constexpr size_t kPairMinBlocks = 3072;
-struct ModUpRows {
-  uint32_t n;
-  uint16_t row[kMaxRows];     // output row (workspace row)
-  uint16_t row2[kMaxRows];    // second output row or kNoRow
-  uint16_t src[kMaxRows];     // workspace row of the digit's first source limb
-  uint8_t mod[kMaxRows];
-  uint8_t mod2[kMaxRows];
-  uint8_t digit[kMaxRows];
-};
+// tiles up to which the inner products take two sets of wavefronts each: two
+// a CU.  One special basis of 8 limbs at N = 2^16 (512 tiles) 22.6 -> 18.9 us;
+// 24 limbs (1536 tiles) 45.9 -> 49.1 us, so larger launches do not.
+constexpr size_t kSplitMaxBlocks = 512;
 
 template <int LOGN>
 __global__ __launch_bounds__(kNttThreads) void k_ks_intt_gather(
-    uint64_t *__restrict__ ws, KsBatch kb, KsGeom kg,
-    const ModConst *__restrict__ mc, const uint64_t *__restrict__ itw,
-    const uint64_t *__restrict__ itws, const uint64_t *__restrict__ itt,
-    const uint64_t *__restrict__ itts) {
+    uint64_t *__restrict__ ws, KsBatch kb, KsGeom kg, const ModConst *__restrict__ mc,
+    const Tw *__restrict__ itn, const Tw *__restrict__ itt) {
   using G = Pass<split_b(LOGN), LOGN, false>;
   constexpr int P = G::P;
   __shared__ uint64_t lds[G::LDS_WORDS];
+  __shared__ Tw lw[G::TW_LEN];
   const int li = blockIdx.z;  // limb i (modulus i)
+  G::fill_inverse(lw, itn + (size_t)li * kRootLen);
   const uint32_t b = blockIdx.y;
-  const uint64_t q = mc[li].q;
-  const Qn qm = qn(mc[li]);
   const size_t roff = (size_t)li * G::N;
   const uint64_t *d = kb.d[b];
   const uint32_t galois = kb.galois[b];
@@ -91,33 +83,37 @@ __global__ __launch_bounds__(kNttThreads) void k_ks_intt_gather(
       cp[a] = c0[a];
     }
   }
-  uint64_t x[P];
+  with_arith(mc[li], [&](auto ar) {
+    using Ar = decltype(ar);
+    typename Ar::E x[P];
 #pragma unroll
-  for (int i = 0; i < P; i++)
-    x[i] = d[roff + galois_src((uint32_t)G::gaddr(g, G::ipoint(r, i)), galois, LOGN)];
-  G::to_blocked(lds, x, c, r);
-  G::inverse(lds, x, c, r, g, itw + roff, itws + roff, qm);
-  G::twist(x, g, r, itt + roff, itts + roff, qm);
+    for (int i = 0; i < P; i++)
+      x[i] = ar.load(d[roff + galois_src((uint32_t)G::gaddr(g, G::ipoint(r, i)), galois, LOGN)]);
+    __syncthreads();
+    G::to_blocked(lds, x, c, r);
+    G::template inverse<Ar, Ar::kCanonical>(lds, x, c, r, itn + (size_t)li * kRootLen, lw, ar);
+    G::twist(x, g, r, itt + roff, ar);
 #pragma unroll
-  for (int i = 0; i < P; i++) y[roff + G::gaddr(g, G::ipoint(r, i))] = x[i];
+    for (int i = 0; i < P; i++) y[roff + G::gaddr(g, G::ipoint(r, i))] = Ar::bits(x[i]);
+  });
 }
 
 // Fast basis conversion of a thread's P points (interleaved layout of the
 // strided pass) at load time, into NT target moduli at once:
-//   x[t][i] = REDC(sum_{a < na} src[a N + pos_i] cv[t][a cstride]) in [0, q_t)
-// (constants in Montgomery form; the sum stays below q_t 2^64).  Points are
-// taken CH at a time, with the CH loads of one source limb issued together
-// so that their latencies overlap (one load, then a wait, per product
-// leaves the conversion latency-bound); each loaded word serves every
-// target.
+//   x[t][i] = sum_{a < na} src[a N + pos_i] c_a  mod q_t
+// in [0, q_t), from cv[t][a cstride].w (Montgomery form; the sum stays below
+// q_t 2^64).  Points are taken CH at a time, with the CH loads of one source
+// limb issued together so that their latencies overlap (one load, then a
+// wait, per product leaves the conversion latency-bound); each loaded word
+// serves every target.  This form takes any moduli.
 template <class G, int NT>
-__device__ __forceinline__ void bconv_points(uint64_t (&x)[NT][G::P],
-                                             const uint64_t *__restrict__ src,
-                                             const uint64_t *const (&cv)[NT], uint32_t cstride,
-                                             uint32_t na, int g, int r,
-                                             const ModConst (&m)[NT]) {
+__device__ __forceinline__ void bconv_words(uint64_t (&x)[NT][G::P],
+                                            const uint64_t *__restrict__ src,
+                                            const ConvC *const (&cv)[NT], uint32_t cstride,
+                                            uint32_t na, int g, int r,
+                                            const ModConst (&m)[NT]) {
   constexpr int P = G::P;
-  constexpr int CH = NT == 1 ? P : P / 2;
+  constexpr int CH = P / NT;
 #pragma unroll
   for (int c0 = 0; c0 < P; c0 += CH) {
     u128 acc[NT][CH];
@@ -131,7 +127,7 @@ __device__ __forceinline__ void bconv_points(uint64_t (&x)[NT][G::P],
       for (int k = 0; k < CH; k++) v[k] = src[(size_t)a * G::N + G::gaddr(g, G::ipoint(r, c0 + k))];
 #pragma unroll
       for (int t = 0; t < NT; t++) {
-        const uint64_t c = cv[t][(size_t)a * cstride];
+        const uint64_t c = cv[t][(size_t)a * cstride].w;
 #pragma unroll
         for (int k = 0; k < CH; k++) mac_wide(acc[t][k], v[k], c);
       }
@@ -146,23 +142,22 @@ __device__ __forceinline__ void bconv_points(uint64_t (&x)[NT][G::P],
 // The same sums for moduli below 2^60 (sources v and constants c below
 // 2^60), with both factors split into 30-bit halves, v = v1 2^30 + v0 and
 // c = c1 2^30 + c0:
-//   sum_a v c = L + 2^30 (M1 + M2) + 2^60 H,
-//   L = sum v0 c0, M1 = sum v0 c1, M2 = sum v1 c0, H = sum v1 c1.
-// Each column is below na (2^30 - 1)^2 < 2^64 for na <= 16 sources (a
-// digit or the special basis holds at most 16 primes), so every partial
-// product is one 32 x 32 + 64-bit multiply-add into its column, with no
-// carries between columns; the columns are combined into the 128-bit sum
-// (the same integer as above, so the same REDC result) once per point.
-// Four 64-bit columns take twice the registers of one 128-bit sum, so the
-// points are taken in chunks of half the size.
-template <class G, int NT, bool UNROLL2>
-__device__ __forceinline__ void bconv_points30(uint64_t (&x)[NT][G::P],
-                                               const uint64_t *__restrict__ src,
-                                               const uint64_t *const (&cv)[NT], uint32_t cstride,
-                                               uint32_t na, int g, int r,
-                                               const ModConst (&m)[NT]) {
+//   sum_a v c = L + 2^30 M + 2^60 H,
+//   L = sum v0 c0, H = sum v1 c1, M = sum (v0 + v1)(c0 + c1) - L - H.
+// L and H stay below na 2^60 <= 2^64 (a digit or the special basis holds at
+// most 16 primes); for na <= 8 the true M does too, so its column may wrap on
+// the way and three multiply-adds a product do.  Above 8 sources the cross
+// products keep two columns (four multiply-adds).  The columns are combined
+// into the 128-bit sum (the same integer as above, so the same REDC result)
+// once per point.
+template <class G, int NT>
+__device__ __forceinline__ void bconv_halves(uint64_t (&x)[NT][G::P],
+                                             const uint64_t *__restrict__ src,
+                                             const ConvC *const (&cv)[NT], uint32_t cstride,
+                                             uint32_t na, int g, int r,
+                                             const ModConst (&m)[NT]) {
   constexpr int P = G::P;
-  constexpr int CH = NT == 1 ? P / 2 : P / 4;
+  constexpr int CH = (P < 8 ? P : 8) / NT;
   constexpr uint32_t kLow30 = (1u << 30) - 1;
 #pragma unroll
   for (int c0 = 0; c0 < P; c0 += CH) {
@@ -171,36 +166,54 @@ __device__ __forceinline__ void bconv_points30(uint64_t (&x)[NT][G::P],
     for (int t = 0; t < NT; t++)
 #pragma unroll
       for (int k = 0; k < CH; k++) lo[t][k] = m1[t][k] = m2[t][k] = hi[t][k] = 0;
-    // one source limb: its CH words, split, into every target's columns
-    auto source = [&](uint32_t a) {
-      uint32_t v0[CH], v1[CH];
+    uint64_t v[CH], nx[CH];
+#pragma unroll
+    for (int k = 0; k < CH; k++) nx[k] = src[G::gaddr(g, G::ipoint(r, c0 + k))];
+    auto next = [&](uint32_t a) {  // takes limb a's words and loads limb a + 1's
+      const size_t n = (size_t)(a + 1 < na ? a + 1 : a) * G::N;
 #pragma unroll
       for (int k = 0; k < CH; k++) {
-        const uint64_t v = src[(size_t)a * G::N + G::gaddr(g, G::ipoint(r, c0 + k))];
-        v0[k] = (uint32_t)v & kLow30;
-        v1[k] = (uint32_t)(v >> 30);
-      }
-#pragma unroll
-      for (int t = 0; t < NT; t++) {
-        const uint64_t c = cv[t][(size_t)a * cstride];
-        const uint32_t cl = (uint32_t)c & kLow30, ch = (uint32_t)(c >> 30);
-#pragma unroll
-        for (int k = 0; k < CH; k++) {
-          lo[t][k] += (uint64_t)v0[k] * cl;
-          m1[t][k] += (uint64_t)v0[k] * ch;
-          m2[t][k] += (uint64_t)v1[k] * cl;
-          hi[t][k] += (uint64_t)v1[k] * ch;
-        }
+        v[k] = nx[k];
+        nx[k] = src[n + G::gaddr(g, G::ipoint(r, c0 + k))];
       }
     };
-    // two source limbs per iteration put twice the loads in flight; the
-    // paired ModUp, held to 128 registers for a fourth wave per SIMD, takes
-    // one (the unrolled loop would spill more there)
-    if constexpr (UNROLL2) {
-#pragma unroll 2
-      for (uint32_t a = 0; a < na; a++) source(a);
+    if (na <= 8) {
+      for (uint32_t a = 0; a < na; a++) {
+        next(a);
+#pragma unroll
+        for (int t = 0; t < NT; t++) {
+          const uint64_t c = cv[t][(size_t)a * cstride].w;
+          const uint32_t cl = (uint32_t)c & kLow30, ch = (uint32_t)(c >> 30), cs = cl + ch;
+#pragma unroll
+          for (int k = 0; k < CH; k++) {
+            const uint32_t v0 = (uint32_t)v[k] & kLow30, v1 = (uint32_t)(v[k] >> 30);
+            lo[t][k] += (uint64_t)v0 * cl;
+            hi[t][k] += (uint64_t)v1 * ch;
+            m1[t][k] += (uint64_t)(v0 + v1) * cs;
+          }
+        }
+      }
+#pragma unroll
+      for (int t = 0; t < NT; t++)
+#pragma unroll
+        for (int k = 0; k < CH; k++) m1[t][k] -= lo[t][k] + hi[t][k];
     } else {
-      for (uint32_t a = 0; a < na; a++) source(a);
+      for (uint32_t a = 0; a < na; a++) {
+        next(a);
+#pragma unroll
+        for (int t = 0; t < NT; t++) {
+          const uint64_t c = cv[t][(size_t)a * cstride].w;
+          const uint32_t cl = (uint32_t)c & kLow30, ch = (uint32_t)(c >> 30);
+#pragma unroll
+          for (int k = 0; k < CH; k++) {
+            const uint32_t v0 = (uint32_t)v[k] & kLow30, v1 = (uint32_t)(v[k] >> 30);
+            lo[t][k] += (uint64_t)v0 * cl;
+            m1[t][k] += (uint64_t)v0 * ch;
+            m2[t][k] += (uint64_t)v1 * cl;
+            hi[t][k] += (uint64_t)v1 * ch;
+          }
+        }
+      }
     }
 #pragma unroll
     for (int t = 0; t < NT; t++)
@@ -220,307 +233,552 @@ __device__ __forceinline__ void bconv_points30(uint64_t (&x)[NT][G::P],
   }
 }
 
-template <class G, int NT, bool S30, bool UNROLL2 = true>
-__device__ __forceinline__ void bconv(uint64_t (&x)[NT][G::P], const uint64_t *__restrict__ src,
-                                      const uint64_t *const (&cv)[NT], uint32_t cstride,
-                                      uint32_t na, int g, int r, const ModConst (&m)[NT]) {
-  if constexpr (S30)
-    bconv_points30<G, NT, UNROLL2>(x, src, cv, cstride, na, g, r, m);
-  else
-    bconv_points<G, NT>(x, src, cv, cstride, na, g, r, m);
-}
-
-// the paired 30-bit ModUp is held to 128 VGPRs (4 waves per SIMD instead of
-// 3, at 8 bytes of spill a lane): measured 6 % faster
-template <int LOGN, bool PAIR, bool S30>
-__global__ __launch_bounds__(kNttThreads)
-__attribute__((amdgpu_waves_per_eu(PAIR && S30 ? 4 : 1))) void k_modup_strided(
-    uint64_t *__restrict__ ws, ModUpRows rows, const uint64_t *__restrict__ conv, KsGeom kg,
-    const ModConst *__restrict__ mc, const uint64_t *__restrict__ tw,
-    const uint64_t *__restrict__ tws) {
-  using G = Pass<split_a(LOGN), LOGN, true>;
+// The sums for targets on doubles, within 1/2 q.  A source word is centred
+// and split, v = v1 2^25 + v0 + (2^49 + 2^24) with |v0|, |v1| about 2^24; the
+// constant is centred and split likewise, and
+//   sum v c = L + 2^25 M + 2^50 H + K,
+//   L = sum v0 c0, H = sum v1 c1, M = sum (v0 + v1)(c0 + c1) - L - H,
+// three FP64 multiply-adds a product, every column an exact integer (the
+// bounds, over this context's constants, are checked when it is made:
+// hck_context::conv_f).  K undoes the centring.  A source whose prime is not
+// in the floating-point range has its bits from 50 on as
+// one more small factor with the constant c 2^50 mod t.  The columns are
+// combined by Horner's rule modulo q, where products by 2^25 are exact.
+template <class G, int NT>
+__device__ __forceinline__ void bconv_float(double (&x)[NT][G::P],
+                                            const uint64_t *__restrict__ src,
+                                            const ConvC *const (&cv)[NT], uint32_t cstride,
+                                            uint32_t na, const ModConst *__restrict__ ms, int g,
+                                            int r, const ModConst (&m)[NT]) {
   constexpr int P = G::P;
-  __shared__ uint64_t lds[G::LDS_WORDS];
-  const int k = blockIdx.y;
-  const int j = rows.digit[k];
-  const uint32_t na = min(kg.alpha, kg.nq - j * kg.alpha);
-  const int mi = rows.mod[k];
-  const ModConst m = mc[mi];
-  const uint64_t *cv = conv + (size_t)j * kg.alpha * kg.nm + mi;
-  const uint64_t *src = ws + (size_t)rows.src[k] * G::N;
-  const int c = G::sub(threadIdx.x), r = G::lane(threadIdx.x);
-  const int g = blockIdx.x * G::TR + c;
-  if constexpr (!PAIR) {
-    uint64_t x[1][P];
-    const uint64_t *const cvs[1] = {cv};
-    const ModConst ms[1] = {m};
-    bconv<G, 1, S30>(x, src, cvs, kg.nm, na, g, r, ms);
-    G::forward(lds, x[0], c, r, g, tw + (size_t)mi * G::N, tws + (size_t)mi * G::N, qn(m));
-    uint64_t *out = ws + (size_t)rows.row[k] * G::N;
+  constexpr int CH = (P < 8 ? P : 8) / NT;
+  constexpr uint64_t kExp = 0x4330000000000000ull;          // 2^52 + (low bits)
+  constexpr double kOff = 4503599627370496.0 + 16777216.0;  // 2^52 + 2^24
 #pragma unroll
-    for (int v = 0; v < P; v++) out[G::gaddr(g, G::bpoint(r, v))] = x[0][v];
-  } else {
-    const bool two = rows.row2[k] != kNoRow;
-    const int mi2 = two ? rows.mod2[k] : mi;
-    const ModConst m2 = mc[mi2];
-    const uint64_t *cv2 = conv + (size_t)j * kg.alpha * kg.nm + mi2;
-    uint64_t x[2][P];
-    const uint64_t *const cvs[2] = {cv, cv2};
-    const ModConst ms[2] = {m, m2};
-    bconv<G, 2, S30, false>(x, src, cvs, kg.nm, na, g, r, ms);
-    G::forward(lds, x[0], c, r, g, tw + (size_t)mi * G::N, tws + (size_t)mi * G::N, qn(m));
-    uint64_t *out = ws + (size_t)rows.row[k] * G::N;
+  for (int c0 = 0; c0 < P; c0 += CH) {
+    double lo[NT][CH], mi[NT][CH], hi[NT][CH];
 #pragma unroll
-    for (int v = 0; v < P; v++) out[G::gaddr(g, G::bpoint(r, v))] = x[0][v];
-    if (!two) return;
-    G::forward(lds, x[1], c, r, g, tw + (size_t)mi2 * G::N, tws + (size_t)mi2 * G::N, qn(m2));
-    uint64_t *out2 = ws + (size_t)rows.row2[k] * G::N;
+    for (int t = 0; t < NT; t++)
 #pragma unroll
-    for (int v = 0; v < P; v++) out2[G::gaddr(g, G::bpoint(r, v))] = x[1][v];
+      for (int k = 0; k < CH; k++) lo[t][k] = mi[t][k] = hi[t][k] = 0.0;
+    uint64_t v[CH], nx[CH];
+#pragma unroll
+    for (int k = 0; k < CH; k++) nx[k] = src[G::gaddr(g, G::ipoint(r, c0 + k))];
+    for (uint32_t a = 0; a < na; a++) {
+      const size_t n = (size_t)(a + 1 < na ? a + 1 : a) * G::N;
+#pragma unroll
+      for (int k = 0; k < CH; k++) {
+        v[k] = nx[k];
+        nx[k] = src[n + G::gaddr(g, G::ipoint(r, c0 + k))];
+      }
+      const bool wide = ms[a].qd == 0.0;  // uniform
+#pragma unroll
+      for (int k = 0; k < CH; k++) {
+        const double v0 = __longlong_as_double((long long)((v[k] & 0x1ffffff) | kExp)) - kOff;
+        const uint64_t top = wide ? (v[k] >> 25) & 0x1ffffff : v[k] >> 25;
+        const double v1 = __longlong_as_double((long long)(top | kExp)) - kOff;
+        const double vs = v0 + v1;
+#pragma unroll
+        for (int t = 0; t < NT; t++) {
+          const ConvC &c = cv[t][(size_t)a * cstride];
+          lo[t][k] = __builtin_fma(v0, c.c0, lo[t][k]);
+          hi[t][k] = __builtin_fma(v1, c.c1, hi[t][k]);
+          mi[t][k] = __builtin_fma(vs, c.cs, mi[t][k]);
+        }
+        if (wide) {
+          const double v2 = (double)(uint32_t)(v[k] >> 50);
+#pragma unroll
+          for (int t = 0; t < NT; t++) {
+            const ConvC &c = cv[t][(size_t)a * cstride];
+            lo[t][k] = __builtin_fma(v2, c.e0, lo[t][k]);
+            mi[t][k] = __builtin_fma(v2, c.es, mi[t][k]);
+          }
+        }
+      }
+    }
+#pragma unroll
+    for (int t = 0; t < NT; t++) {
+      const ArF ar{m[t].qd, m[t].qid};
+      const double c25 = 33554432.0, q25 = 33554432.0 * m[t].qid;
+      const double kt = cv[t][(size_t)na * cstride].c0;
+#pragma unroll
+      for (int k = 0; k < CH; k++) {
+        const double mid = mi[t][k] - lo[t][k] - hi[t][k];
+        const double u = __builtin_fma(-__builtin_rint(hi[t][k] * q25), ar.q, hi[t][k] * c25) + mid;
+        const double w = __builtin_fma(-__builtin_rint(u * q25), ar.q, u * c25) + (lo[t][k] + kt);
+        x[t][c0 + k] = ar.reduce(w);
+        asm volatile("" ::"v"(x[t][c0 + k]) : "memory");  // one chunk at a time
+      }
+    }
   }
 }
 
-template <int LOGN>
-__global__ __launch_bounds__(kNttThreads) void k_ks_contig_inner(
-    uint64_t *__restrict__ ws, KsBatch kb, KsGeom kg, const ModConst *__restrict__ mc,
-    const uint64_t *__restrict__ tw, const uint64_t *__restrict__ tws,
-    const uint64_t *__restrict__ tt, const uint64_t *__restrict__ tts,
-    const uint64_t *__restrict__ itw, const uint64_t *__restrict__ itws,
-    const uint64_t *__restrict__ itt, const uint64_t *__restrict__ itts) {
+// The conversion in a target's arithmetic.  S30: every modulus is below 2^60
+// and the columns of this context's constants stay exact in doubles; other
+// contexts convert on whole words.
+template <class G, int NT, bool S30, class Ar>
+__device__ __forceinline__ void bconv(typename Ar::E (&x)[NT][G::P],
+                                      const uint64_t *__restrict__ src,
+                                      const ConvC *const (&cv)[NT], uint32_t cstride, uint32_t na,
+                                      const ModConst *__restrict__ ms, int g, int r,
+                                      const ModConst (&m)[NT], Ar ar) {
+  if constexpr (Ar::kFloat && S30) {
+    bconv_float<G, NT>(x, src, cv, cstride, na, ms, g, r, m);
+  } else {
+    uint64_t u[NT][G::P];
+    if constexpr (S30)
+      bconv_halves<G, NT>(u, src, cv, cstride, na, g, r, m);
+    else
+      bconv_words<G, NT>(u, src, cv, cstride, na, g, r, m);
+#pragma unroll
+    for (int t = 0; t < NT; t++)
+#pragma unroll
+      for (int i = 0; i < G::P; i++) x[t][i] = ar.load(u[t][i]);
+  }
+}
+
+// The arithmetic of modulus m in a key-switching kernel: contexts whose
+// moduli all lie below 2^60 (S30) need no narrower integer class.
+template <bool S30, class F>
+__device__ __forceinline__ void with_ks_arith(const ModConst &m, F &&f) {
+  if (m.qd != 0.0)
+    f(ArF{m.qd, m.qid});
+  else if (S30 || m.q < (1ull << 60))
+    f(ArI<16>{m.q, m.nq});
+  else
+    f(ArI<8>{m.q, m.nq});
+}
+
+// The conversions' pass: three layouts, except where two targets share a
+// workgroup (two arrays of 16 points in two layouts keep more loads of a
+// source in flight per register: 224 us against 254 us for 8 slots of 72 rows)
+// and for conversions on whole words.
+template <int LOGN, bool PAIR, bool S30>
+using ConvPass = typename PassPick<PAIR || !S30 ? 2 : pass_kind(split_a(LOGN), true),
+                                   split_a(LOGN), LOGN, true>::type;
+
+// K3: workgroup y converts the targets of group y (one, or two of one
+// arithmetic) of slot z.  Two targets share the reads of the sources.
+template <int LOGN, bool PAIR, bool S30>
+__global__ __launch_bounds__((ConvPass<LOGN, PAIR, S30>::THREADS))
+__attribute__((amdgpu_waves_per_eu(!PAIR && S30 ? 4 : 3))) void k_modup_strided(
+    uint64_t *__restrict__ ws, const ConvGroup *__restrict__ groups,
+    const ConvC *__restrict__ conv, KsGeom kg, const ModConst *__restrict__ mc,
+    const Tw *__restrict__ tw) {
+  using G = ConvPass<LOGN, PAIR, S30>;
+  constexpr int P = G::P, NT = PAIR ? 2 : 1;
+  __shared__ uint64_t lds[G::LDS_WORDS];
+  __shared__ Tw lw[NT][G::TW_LEN];
+  const ConvGroup gr = groups[blockIdx.y];
+  const uint32_t lo = gr.digit * kg.alpha;
+  const uint32_t na = min(kg.alpha, kg.nq - lo);
+  uint64_t *slot = ws + (size_t)blockIdx.z * kg.slot_rows * G::N;
+  const ConvC *cd = conv + (size_t)gr.digit * (kg.alpha + 1) * kg.nm;
+  const uint64_t *src = slot + (size_t)lo * G::N;
+  const int c = G::sub(threadIdx.x), r = G::lane(threadIdx.x);
+  const int g = blockIdx.x * G::TR + c;
+  const int mi[2] = {gr.mod[0], gr.mod[1]};
+  const ConvC *cvs[NT];
+  ModConst ms[NT];
+#pragma unroll
+  for (int t = 0; t < NT; t++) {
+    cvs[t] = cd + mi[t];
+    ms[t] = mc[mi[t]];
+    G::fill_forward(lw[t], tw + (size_t)mi[t] * kTwLen);
+  }
+  with_ks_arith<S30>(ms[0], [&](auto ar) {
+    using Ar = decltype(ar);
+    typename Ar::E x[NT][P];
+    bconv<G, NT, S30>(x, src, cvs, kg.nm, na, mc + lo, g, r, ms, ar);
+#pragma unroll
+    for (int t = 0; t < NT; t++) {
+      if (t == 1 && gr.n < 2) break;
+      Ar at = ar;
+      if (t == 1) {
+        if constexpr (Ar::kFloat) at = Ar{ms[NT - 1].qd, ms[NT - 1].qid};
+        else at = Ar{ms[NT - 1].q, ms[NT - 1].nq};
+      }
+      if (t == 0) __syncthreads();
+      G::template forward<Ar, Ar::kCanonical>(lds, x[t], c, r, tw + (size_t)mi[t] * kTwLen, lw[t],
+                                              at);
+      uint64_t *out = slot + (size_t)gr.row[t] * G::N;
+#pragma unroll
+      for (int v = 0; v < P; v++) out[G::gaddr(g, G::bpoint(r, v))] = Ar::bits(x[t][v]);
+    }
+  });
+}
+
+// K4 and K7: per extended limb t, the forward contiguous pass of each digit
+// and the inner product with the slot's key; then for a special limb the
+// inverse contiguous pass of both accumulators, and for a Q limb with TAIL
+// ModDown's tail on them in registers (without, they are stored).  The launch
+// covers limbs first, first + 1, ... of the list special limbs, then Q limbs.
+//
+// A workgroup's time is a chain of passes (one a digit, one a polynomial),
+// each waiting for its own loads.  In launches that leave the chip room
+// (SPLIT) a tile takes two sets of wavefronts: set h takes the digits h,
+// h + 2, ..., the sets exchange partial sums through LDS, and set h finishes
+// polynomial h, so the chain is half as long.
+template <int LOGN, bool TAIL, bool SPLIT>
+__global__ __launch_bounds__(kNttThreads * (SPLIT ? 2 : 1))
+__attribute__((amdgpu_waves_per_eu(4))) void k_ks_contig_inner(
+    uint64_t *__restrict__ ws, KsBatch kb, KsGeom kg, uint32_t first, int canonical,
+    const ModConst *__restrict__ mc, const Tw *__restrict__ tw, const Tw *__restrict__ tt,
+    const Tw *__restrict__ itn, const Tw *__restrict__ itt, const Tw *__restrict__ pinv) {
   using G = Pass<split_b(LOGN), LOGN, false>;
   constexpr int P = G::P;
-  __shared__ uint64_t lds[G::LDS_WORDS];
-  // With 8 points a thread (three-layout passes) a workgroup covers TILE
-  // consecutive words of a row, a wavefront 512 of them.  Each digit's two
+  __shared__ uint64_t lds_[SPLIT ? 2 : 1][G::LDS_WORDS];
+  // A workgroup of whole wavefronts' sub-transforms covers TILE consecutive
+  // words of a row, a wavefront WTILE of them.  Each digit's two
   // key rows over those words are copied into LDS by direct global-to-LDS
   // loads issued before the digit's forward pass, so the copy runs under the
   // transform without holding registers; each wavefront reads only the words
-  // it copied (no workgroup barrier).  The two rows take 32 KiB, which still
-  // leaves room for as many workgroups per CU as the registers allow.
-  constexpr bool KEY_LDS = G::P == 8 && G::T * G::TR == kNttThreads && split_b(LOGN) >= 7;
-  constexpr int TILE = kNttThreads * P;
+  // it copied (no workgroup barrier).
+  constexpr bool KEY_LDS = !SPLIT && split_b(LOGN) >= 7;
+  constexpr int TILE = kNttThreads * P, WTILE = 64 * P;
   __shared__ uint64_t ktile[KEY_LDS ? 2 * TILE : 1];
-  // the special limbs, which also run an inverse pass, are dispatched first
-  // so that the shorter workgroups fill in behind them
-  const uint32_t t = blockIdx.z < kg.K ? kg.nq + blockIdx.z : blockIdx.z - kg.K;
+  __shared__ Tw lw[G::TW_LEN];
+  const uint32_t z = first + blockIdx.z;
+  const uint32_t t = z < kg.K ? kg.nq + z : z - kg.K;
   const uint32_t b = blockIdx.y;
   const uint32_t mi = t < kg.nq ? t : kg.L + (t - kg.nq);
   const ModConst m = mc[mi];
-  const int c = G::sub(threadIdx.x), r = G::lane(threadIdx.x);
+  const int tid = threadIdx.x % kNttThreads;
+  const uint32_t set =
+      SPLIT ? __builtin_amdgcn_readfirstlane(threadIdx.x / kNttThreads) : 0;
+  uint64_t *lds = lds_[set];
+  const int c = G::sub(tid), r = G::lane(tid);
   const int g = blockIdx.x * G::TR + c;
   const size_t krow = (size_t)kg.nm * G::N;
   uint64_t *slot = ws + (size_t)b * kg.slot_rows * G::N;
   const uint64_t *d = kb.d[b];
   const uint64_t *key = kb.key[b];
   const uint32_t galois = kb.galois[b];
-  uint64_t a0[P], a1[P], x[P];
-#pragma unroll
-  for (int i = 0; i < P; i++) a0[i] = a1[i] = 0;
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
   const size_t tile0 = (size_t)blockIdx.x * TILE;  // first word of the tile in a row
-  for (uint32_t j = 0; j < kg.dnum; j++) {
-    const uint32_t lo = j * kg.alpha;
-    if (lo >= kg.nq) break;
-    const uint32_t hi = min(lo + kg.alpha, kg.nq);
-    const uint64_t *kbp = key + 2 * j * krow + (size_t)mi * G::N;
-    const uint64_t *kap = kbp + krow;
-    // this wavefront's 512 words of each key row: 4 loads of 16 bytes a lane
-    // (1 KiB a load), lane l's bytes landing at 16 l.  Loads complete in
-    // issue order, so the copy is issued after the digit's own loads (a wait
-    // for those does not wait for it) and before the transform it hides under.
-    auto copy_keys = [&]() {
-      if constexpr (KEY_LDS) {
+  tw += (size_t)mi * kTwLen;
+  tt += (size_t)mi * G::N;
+  itn += (size_t)mi * kRootLen;
+  if (set == 0) G::fill_forward(lw, tw);
+  __syncthreads();
+  with_arith(m, [&](auto ar) {
+    using Ar = decltype(ar);
+    using E = typename Ar::E;
+    E a0[P], a1[P], x[P];
 #pragma unroll
-        for (int rr = 0; rr < 2; rr++) {
-          const uint64_t *src = (rr ? kap : kbp) + tile0 + wave * 512 + 2 * (threadIdx.x % 64);
+    for (int i = 0; i < P; i++) a0[i] = a1[i] = 0;
+    for (uint32_t j = set; j < kg.dnum; j += SPLIT ? 2 : 1) {
+      const uint32_t lo = j * kg.alpha;
+      if (lo >= kg.nq) break;
+      const uint32_t hi = min(lo + kg.alpha, kg.nq);
+      const uint64_t *kbp = key + 2 * j * krow + (size_t)mi * G::N;
+      const uint64_t *kap = kbp + krow;
+      uint64_t k0[P], k1[P];
+      // this wavefront's words of each key row in loads of 16 bytes a lane
+      // (1 KiB a load), lane l's bytes landing at 16 l.  Loads complete in
+      // issue order, so the copy is issued after the digit's own loads (a wait
+      // for those does not wait for it) and before the transform it hides under.
+      auto copy_keys = [&]() {
+        if constexpr (KEY_LDS) {
 #pragma unroll
-          for (int i = 0; i < 4; i++)
-            __builtin_amdgcn_global_load_lds(
-                (const void *)(src + 128 * i),
-                (__attribute__((address_space(3))) void *)&ktile[rr * TILE + wave * 512 + 128 * i],
-                16, 0, 0);
+          for (int rr = 0; rr < 2; rr++) {
+            const uint64_t *src = (rr ? kap : kbp) + tile0 + wave * WTILE + 2 * (threadIdx.x % 64);
+#pragma unroll
+            for (int i = 0; i < P / 2; i++)
+              __builtin_amdgcn_global_load_lds(
+                  (const void *)(src + 128 * i),
+                  (__attribute__((address_space(3))) void *)&ktile[rr * TILE + wave * WTILE + 128 * i],
+                  16, 0, 0);
+          }
+        } else {
+#pragma unroll
+          for (int i = 0; i < P; i++) {
+            const size_t pos = G::gaddr(g, G::ipoint(r, i));
+            k0[i] = kbp[pos];
+            k1[i] = kap[pos];
+          }
+        }
+      };
+      if (t >= lo && t < hi) {
+        copy_keys();
+#pragma unroll
+        for (int i = 0; i < P; i++)
+          x[i] = ar.load(d[(size_t)t * G::N +
+                           galois_src((uint32_t)G::gaddr(g, G::ipoint(r, i)), galois, LOGN)]);
+      } else {
+        const uint64_t *e = slot + ((size_t)kg.off_ext + j * kg.ne + t) * G::N;
+#pragma unroll
+        for (int i = 0; i < P; i++) x[i] = Ar::raw(e[G::gaddr(g, G::ipoint(r, i))]);
+        G::twist(x, g, r, tt, ar);
+        copy_keys();
+        G::template forward<Ar, twisted_bound<Ar>()>(lds, x, c, r, tw, lw, ar);
+#pragma unroll
+        for (int v = 0; v < P; v++) x[v] = ar.settle(x[v]);
+        G::to_interleaved(lds, x, c, r);
+      }
+      // the compiler does not order reads of ktile after the copies into it:
+      // wait for this wavefront's copies (all its earlier loads are in use by
+      // now) before the first read
+      if constexpr (KEY_LDS) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+#pragma unroll
+      for (int i = 0; i < P; i++) {
+        if constexpr (KEY_LDS) {
+          const size_t pos = G::gaddr(g, G::ipoint(r, i));
+          k0[i] = ktile[pos - tile0];
+          k1[i] = ktile[TILE + pos - tile0];
+        }
+        if constexpr (Ar::kFloat) {
+          // |x| <= q and a centred key: products within 0.7 q
+          a0[i] += ar.mul2(x[i], Ar::raw(k0[i]));
+          a1[i] += ar.mul2(x[i], Ar::raw(k1[i]));
+        } else {
+          a0[i] = add_mod(a0[i], redc(mul_wide(x[i], k0[i]), m.q, m.qinv), m.q);
+          a1[i] = add_mod(a1[i], redc(mul_wide(x[i], k1[i]), m.q, m.qinv), m.q);
         }
       }
-    };
-    if (t >= lo && t < hi) {
-      copy_keys();
+      if constexpr (Ar::kFloat) {
+        // within 6.1 q at all times (each set's partial sums within 3.3 q)
+        if ((j & 7) >= (SPLIT ? 6 : 7)) {
+#pragma unroll
+          for (int i = 0; i < P; i++) {
+            a0[i] = ar.reduce(a0[i]);
+            a1[i] = ar.reduce(a1[i]);
+          }
+        }
+      }
+    }
+    if constexpr (SPLIT) {
+      // set 0 gives its sum of polynomial 1 for set 1's of polynomial 0 (the
+      // words go to every wavefront's rows: after all of them are done)
+      __syncthreads();
 #pragma unroll
       for (int i = 0; i < P; i++)
-        x[i] = d[(size_t)t * G::N +
-                 galois_src((uint32_t)G::gaddr(g, G::ipoint(r, i)), galois, LOGN)];
-    } else {
-      const uint64_t *e = slot + ((size_t)kg.off_ext + j * kg.ne + t) * G::N;
+        lds_[set][i * kNttThreads + tid] = Ar::bits(set ? a0[i] : a1[i]);
+      __syncthreads();
 #pragma unroll
-      for (int i = 0; i < P; i++) x[i] = e[G::gaddr(g, G::ipoint(r, i))];
-      G::twist(x, g, r, tt + (size_t)mi * G::N, tts + (size_t)mi * G::N, qn(m));
-      copy_keys();
-      G::forward(lds, x, c, r, g, tw + (size_t)mi * G::N, tws + (size_t)mi * G::N, qn(m));
-#pragma unroll
-      for (int v = 0; v < P; v++) x[v] = reduce4(x[v], qn(m));
-      G::to_interleaved(lds, x, c, r);
-    }
-#pragma unroll
-    for (int i = 0; i < P; i++) {
-      const size_t pos = G::gaddr(g, G::ipoint(r, i));
-      uint64_t kv0, kv1;
-      if constexpr (KEY_LDS) {
-        kv0 = ktile[pos - tile0];
-        kv1 = ktile[TILE + pos - tile0];
-      } else {
-        kv0 = kbp[pos];
-        kv1 = kap[pos];
+      for (int i = 0; i < P; i++) {
+        const E o = Ar::raw(lds_[set ^ 1][i * kNttThreads + tid]);
+        const E own = set ? a1[i] : a0[i];
+        if constexpr (Ar::kFloat) a0[i] = own + o;
+        else a0[i] = add_mod(own, o, m.q);
       }
-      a0[i] = add_mod(a0[i], redc(mul_wide(x[i], kv0), m.q, m.qinv), m.q);
-      a1[i] = add_mod(a1[i], redc(mul_wide(x[i], kv1), m.q, m.qinv), m.q);
+      __syncthreads();
     }
-  }
-  if (t >= kg.nq) {
-    // special limb: ModDown's inverse contiguous pass, while the limb's
-    // blocks are at hand
-    const size_t toff = (size_t)mi * G::N;
-    G::to_blocked(lds, a0, c, r);
-    G::inverse(lds, a0, c, r, g, itw + toff, itws + toff, qn(m));
-    G::twist(a0, g, r, itt + toff, itts + toff, qn(m));
-    G::to_blocked(lds, a1, c, r);
-    G::inverse(lds, a1, c, r, g, itw + toff, itws + toff, qn(m));
-    G::twist(a1, g, r, itt + toff, itts + toff, qn(m));
-  }
-  uint64_t *o0 = slot + ((size_t)kg.off_acc + t) * G::N;
-  uint64_t *o1 = slot + ((size_t)kg.off_acc + kg.ne + t) * G::N;
+    // polynomial p's sums in a
+    auto tail = [&](const E(&a)[P], uint32_t p) {
+      const Tw f = pinv[mi];
+      const uint64_t *cin = slot + ((size_t)kg.off_conv + p * kg.L + t) * G::N;
 #pragma unroll
-  for (int i = 0; i < P; i++) {
-    const size_t pos = G::gaddr(g, G::ipoint(r, i));
-    o0[pos] = a0[i];
-    o1[pos] = a1[i];
-  }
+      for (int i = 0; i < P; i++) x[i] = Ar::raw(cin[G::gaddr(g, G::ipoint(r, i))]);
+      G::twist(x, g, r, tt, ar);
+      G::template forward<Ar, twisted_bound<Ar>()>(lds, x, c, r, tw, lw, ar);
+#pragma unroll
+      for (int v = 0; v < P; v++) x[v] = ar.settle(x[v]);
+      G::to_interleaved(lds, x, c, r);
+      const uint64_t *add = p == 0 ? kb.add0[b] : kb.add1[b];
+      uint64_t *out = (p == 0 ? kb.out0[b] : kb.out1[b]) + (size_t)t * G::N;
+#pragma unroll
+      for (int i = 0; i < P; i++) {
+        const size_t pos = G::gaddr(g, G::ipoint(r, i));
+        E v = ar.mul(ar.sub(a[i], x[i]), f);
+        if (add) v += ar.load(add[(size_t)t * G::N + galois_src((uint32_t)pos, galois, LOGN)]);
+        out[pos] = ar.template canon<3072>(v);
+      }
+    };
+    // special limbs: ModDown's inverse contiguous pass, while the limb's
+    // blocks are at hand
+    auto finish = [&](E(&a)[P], uint32_t p) {
+      if (t >= kg.nq) {
+        if constexpr (Ar::kFloat) {
+#pragma unroll
+          for (int i = 0; i < P; i++) a[i] = ar.reduce(a[i]);
+        }
+        G::to_blocked(lds, a, c, r);
+        G::template inverse<Ar, Ar::kCanonical>(lds, a, c, r, itn, lw, ar);
+        G::twist(a, g, r, itt + (size_t)mi * G::N, ar);
+      }
+      uint64_t *o = slot + ((size_t)kg.off_acc + p * kg.ne + t) * G::N;
+#pragma unroll
+      for (int i = 0; i < P; i++)
+        o[G::gaddr(g, G::ipoint(r, i))] =
+            canonical ? ar.template canon<Ar::kFloat ? 8065 : 2048>(a[i]) : Ar::bits(a[i]);
+    };
+    if constexpr (!TAIL) {
+      __syncthreads();
+      if (set == 0) G::fill_inverse(lw, itn);
+      __syncthreads();
+    }
+    if constexpr (SPLIT) {
+      if constexpr (TAIL) tail(a0, set);
+      else finish(a0, set);
+    } else if constexpr (TAIL) {
+      tail(a0, 0);
+      tail(a1, 1);
+    } else {
+      finish(a0, 0);
+      finish(a1, 1);
+    }
+  });
 }
 
+// K6: workgroup y converts the target limbs of group y (of one poly's groups:
+// one limb, or two consecutive ones of one arithmetic) from one read of the K
+// special limbs.
 template <int LOGN, bool PAIR, bool S30>
-__global__ __launch_bounds__(kNttThreads) void k_moddown_strided(
-    uint64_t *__restrict__ ws, const uint64_t *__restrict__ down_conv,
-    const uint64_t *__restrict__ hneg, KsGeom kg, const ModConst *__restrict__ mc,
-    const uint64_t *__restrict__ tw, const uint64_t *__restrict__ tws) {
-  using G = Pass<split_a(LOGN), LOGN, true>;
-  constexpr int P = G::P;
+__global__ __launch_bounds__((ConvPass<LOGN, PAIR, S30>::THREADS))
+__attribute__((amdgpu_waves_per_eu(!PAIR && S30 ? 4 : 3))) void k_moddown_strided(
+    uint64_t *__restrict__ ws, const ConvC *__restrict__ down_conv,
+    const uint64_t *__restrict__ hneg, const ConvGroup *__restrict__ groups, KsGeom kg,
+    const ModConst *__restrict__ mc, const Tw *__restrict__ tw) {
+  using G = ConvPass<LOGN, PAIR, S30>;
+  constexpr int P = G::P, NT = PAIR ? 2 : 1;
   __shared__ uint64_t lds[G::LDS_WORDS];
-  // with PAIR workgroup y converts target limbs li and li + 1 (if below nq)
-  // of poly p from one read of the K special limbs, else limb li alone
-  const uint32_t per = PAIR ? (kg.nq + 1) / 2 : kg.nq;
-  const uint32_t p = blockIdx.y / per, li = (PAIR ? 2 : 1) * (blockIdx.y % per);
+  __shared__ Tw lw[NT][G::TW_LEN];
+  const uint32_t per = gridDim.y / 2;
+  const uint32_t p = blockIdx.y / per;
+  const ConvGroup gr = groups[blockIdx.y % per];
   uint64_t *slot = ws + (size_t)blockIdx.z * kg.slot_rows * G::N;
-  const ModConst m = mc[li];
-  const uint64_t h = hneg[li];
   const uint64_t *src = slot + ((size_t)kg.off_acc + p * kg.ne + kg.nq) * G::N;
-  const uint64_t *cv = down_conv + li;
   const int c = G::sub(threadIdx.x), r = G::lane(threadIdx.x);
   const int g = blockIdx.x * G::TR + c;
-  if constexpr (!PAIR) {
-    uint64_t x[1][P];
-    const uint64_t *const cvs[1] = {cv};
-    const ModConst ms[1] = {m};
-    bconv<G, 1, S30>(x, src, cvs, kg.nm, kg.K, g, r, ms);
+  const int mi[2] = {gr.mod[0], gr.mod[1]};
+  const ConvC *cvs[NT];
+  ModConst ms[NT];
 #pragma unroll
-    for (int i = 0; i < P; i++) x[0][i] = add_mod(x[0][i], h, m.q);
-    G::forward(lds, x[0], c, r, g, tw + (size_t)li * G::N, tws + (size_t)li * G::N, qn(m));
-    uint64_t *out = slot + ((size_t)kg.off_conv + p * kg.L + li) * G::N;
-#pragma unroll
-    for (int v = 0; v < P; v++) out[G::gaddr(g, G::bpoint(r, v))] = x[0][v];
-  } else {
-    const bool two = li + 1 < kg.nq;
-    const uint32_t li2 = two ? li + 1 : li;
-    const ModConst m2 = mc[li2];
-    const uint64_t h2 = hneg[li2];
-    const uint64_t *cv2 = down_conv + li2;
-    uint64_t x[2][P];
-    const uint64_t *const cvs[2] = {cv, cv2};
-    const ModConst ms[2] = {m, m2};
-    bconv<G, 2, S30>(x, src, cvs, kg.nm, kg.K, g, r, ms);
-#pragma unroll
-    for (int i = 0; i < P; i++) {
-      x[0][i] = add_mod(x[0][i], h, m.q);
-      x[1][i] = add_mod(x[1][i], h2, m2.q);
-    }
-    G::forward(lds, x[0], c, r, g, tw + (size_t)li * G::N, tws + (size_t)li * G::N, qn(m));
-    uint64_t *out = slot + ((size_t)kg.off_conv + p * kg.L + li) * G::N;
-#pragma unroll
-    for (int v = 0; v < P; v++) out[G::gaddr(g, G::bpoint(r, v))] = x[0][v];
-    if (!two) return;
-    G::forward(lds, x[1], c, r, g, tw + (size_t)li2 * G::N, tws + (size_t)li2 * G::N, qn(m2));
-    uint64_t *out2 = slot + ((size_t)kg.off_conv + p * kg.L + li2) * G::N;
-#pragma unroll
-    for (int v = 0; v < P; v++) out2[G::gaddr(g, G::bpoint(r, v))] = x[1][v];
+  for (int t = 0; t < NT; t++) {
+    cvs[t] = down_conv + mi[t];
+    ms[t] = mc[mi[t]];
+    G::fill_forward(lw[t], tw + (size_t)mi[t] * kTwLen);
   }
+  with_ks_arith<S30>(ms[0], [&](auto ar) {
+    using Ar = decltype(ar);
+    typename Ar::E x[NT][P];
+    bconv<G, NT, S30>(x, src, cvs, kg.nm, kg.K, mc + kg.L, g, r, ms, ar);
+#pragma unroll
+    for (int t = 0; t < NT; t++) {
+      if (t == 1 && gr.n < 2) break;
+      Ar at = ar;
+      if (t == 1) {
+        if constexpr (Ar::kFloat) at = Ar{ms[NT - 1].qd, ms[NT - 1].qid};
+        else at = Ar{ms[NT - 1].q, ms[NT - 1].nq};
+      }
+      // minus (P-1)/2: within q (doubles, both terms within 1/2), in [0, 2q)
+      // (integers)
+      typename Ar::E h = at.load(hneg[mi[t]]);
+      if constexpr (Ar::kFloat) h = at.reduce(h);
+#pragma unroll
+      for (int i = 0; i < P; i++) x[t][i] += h;
+      if (t == 0) __syncthreads();
+      G::template forward<Ar, Ar::kFloat ? 2 * Ar::kReduced : 2048>(
+          lds, x[t], c, r, tw + (size_t)mi[t] * kTwLen, lw[t], at);
+      uint64_t *out = slot + ((size_t)kg.off_conv + p * kg.L + mi[t]) * G::N;
+#pragma unroll
+      for (int v = 0; v < P; v++) out[G::gaddr(g, G::bpoint(r, v))] = Ar::bits(x[t][v]);
+    }
+  });
 }
 
+// K7 where the accumulators come from memory (hoisted rotations and shared
+// ModDowns): per Q limb, the forward contiguous pass of conv and the tail.
 template <int LOGN>
 __global__ __launch_bounds__(kNttThreads) void k_moddown_contig_tail(
-    uint64_t *__restrict__ ws, KsBatch kb, RowScale pinv, KsGeom kg,
-    const ModConst *__restrict__ mc, const uint64_t *__restrict__ tw,
-    const uint64_t *__restrict__ tws, const uint64_t *__restrict__ tt,
-    const uint64_t *__restrict__ tts) {
+    uint64_t *__restrict__ ws, KsBatch kb, const Tw *__restrict__ pinv, KsGeom kg,
+    const ModConst *__restrict__ mc, const Tw *__restrict__ tw, const Tw *__restrict__ tt) {
   using G = Pass<split_b(LOGN), LOGN, false>;
   constexpr int P = G::P;
   __shared__ uint64_t lds[G::LDS_WORDS];
+  __shared__ Tw lw[G::TW_LEN];
   const uint32_t p = blockIdx.z & 1, li = blockIdx.z >> 1;
+  G::fill_forward(lw, tw + (size_t)li * kTwLen);
   const uint32_t b = blockIdx.y;
   const uint64_t *slot = ws + (size_t)b * kg.slot_rows * G::N;
-  const uint64_t q = mc[li].q;
-  const Qn qm = qn(mc[li]);
   const int c = G::sub(threadIdx.x), r = G::lane(threadIdx.x);
   const int g = blockIdx.x * G::TR + c;
   const uint64_t *cin = slot + ((size_t)kg.off_conv + p * kg.L + li) * G::N;
-  uint64_t x[P];
-#pragma unroll
-  for (int i = 0; i < P; i++) x[i] = cin[G::gaddr(g, G::ipoint(r, i))];
-  G::twist(x, g, r, tt + (size_t)li * G::N, tts + (size_t)li * G::N, qm);
-  G::forward(lds, x, c, r, g, tw + (size_t)li * G::N, tws + (size_t)li * G::N, qm);
-#pragma unroll
-  for (int v = 0; v < P; v++) x[v] = reduce4(x[v], qm);
-  G::to_interleaved(lds, x, c, r);
   const uint64_t *u = slot + ((size_t)kg.off_acc + p * kg.ne + li) * G::N;
   const uint64_t *add = p == 0 ? kb.add0[b] : kb.add1[b];
   const uint32_t galois = kb.galois[b];
   uint64_t *out = (p == 0 ? kb.out0[b] : kb.out1[b]) + (size_t)li * G::N;
-  const uint64_t w = pinv.w[li], wp = pinv.wp[li];
+  with_arith(mc[li], [&](auto ar) {
+    using Ar = decltype(ar);
+    using E = typename Ar::E;
+    E x[P];
 #pragma unroll
-  for (int i = 0; i < P; i++) {
-    const size_t pos = G::gaddr(g, G::ipoint(r, i));
-    uint64_t v = shoup(sub_mod(u[pos], x[i], q), w, wp, q);
-    if (add) v = add_mod(v, add[(size_t)li * G::N + galois_src((uint32_t)pos, galois, LOGN)], q);
-    out[pos] = v;
-  }
+    for (int i = 0; i < P; i++) x[i] = Ar::raw(cin[G::gaddr(g, G::ipoint(r, i))]);
+    G::twist(x, g, r, tt + (size_t)li * G::N, ar);
+    __syncthreads();
+    G::template forward<Ar, twisted_bound<Ar>()>(lds, x, c, r, tw + (size_t)li * kTwLen, lw, ar);
+#pragma unroll
+    for (int v = 0; v < P; v++) x[v] = ar.settle(x[v]);
+    G::to_interleaved(lds, x, c, r);
+    const Tw f = pinv[li];
+#pragma unroll
+    for (int i = 0; i < P; i++) {
+      const size_t pos = G::gaddr(g, G::ipoint(r, i));
+      E v = ar.mul(ar.sub(ar.load(u[pos]), x[i]), f);
+      if (add) v += ar.load(add[(size_t)li * G::N + galois_src((uint32_t)pos, galois, LOGN)]);
+      out[pos] = ar.template canon<3072>(v);
+    }
+  });
 }
 
-// inner product of hoisted rotations: for extended limb t,
+// inner product of hoisted rotations: for extended limb t of slot b,
 // acc_{0,1}[t] = sum_j phi_g(d~_j)[t] swk_j[t], with d~_j fully transformed in
-// slot 0's ext rows (own limbs: phi_g(c1)) and the result in slot b's acc rows
+// slot 0's ext rows (own limbs: phi_g(c1)) and the result, fully reduced, in
+// slot b's acc rows
 template <int LOGN>
-__global__ __launch_bounds__(256) void k_ks_inner_gather(
-    uint64_t *__restrict__ ws, const uint64_t *__restrict__ c1, uint32_t galois, uint32_t b,
-    const uint64_t *__restrict__ key, KsGeom kg, const ModConst *__restrict__ mc) {
+__global__ __launch_bounds__(256) void k_ks_inner_gather(uint64_t *__restrict__ ws,
+                                                         const uint64_t *__restrict__ c1,
+                                                         KsBatch kb, KsGeom kg,
+                                                         const ModConst *__restrict__ mc) {
   constexpr int N = 1 << LOGN;
   const uint32_t pos = blockIdx.x * 256 + threadIdx.x;
-  const uint32_t t = blockIdx.y;
+  const uint32_t b = blockIdx.y, t = blockIdx.z;
   const uint32_t mi = t < kg.nq ? t : kg.L + (t - kg.nq);
   const ModConst m = mc[mi];
-  const uint32_t src = galois_src(pos, galois, LOGN);
+  const uint32_t src = galois_src(pos, kb.galois[b], LOGN);
+  const uint64_t *key = kb.key[b];
   const size_t krow = (size_t)kg.nm * N;
-  u128 s0, s1;
-  s0.lo = s0.hi = s1.lo = s1.hi = 0;
-  for (uint32_t j = 0; j < kg.dnum; j++) {
-    const uint32_t lo = j * kg.alpha;
-    if (lo >= kg.nq) break;
-    const uint32_t hi = min(lo + kg.alpha, kg.nq);
-    const uint64_t x = (t >= lo && t < hi)
-                           ? c1[(size_t)t * N + src]
-                           : ws[((size_t)kg.off_ext + j * kg.ne + t) * N + src];
-    const uint64_t *kbp = key + 2 * j * krow + (size_t)mi * N;
-    mac_wide(s0, x, kbp[pos]);
-    mac_wide(s1, x, kbp[krow + pos]);
-  }
   uint64_t *slot = ws + (size_t)b * kg.slot_rows * N;
-  slot[((size_t)kg.off_acc + t) * N + pos] = redc(s0, m.q, m.qinv);
-  slot[((size_t)kg.off_acc + kg.ne + t) * N + pos] = redc(s1, m.q, m.qinv);
+  auto digits = [&](auto &&f) {
+    for (uint32_t j = 0; j < kg.dnum; j++) {
+      const uint32_t lo = j * kg.alpha;
+      if (lo >= kg.nq) break;
+      const uint32_t hi = min(lo + kg.alpha, kg.nq);
+      const uint64_t x = (t >= lo && t < hi)
+                             ? c1[(size_t)t * N + src]
+                             : ws[((size_t)kg.off_ext + j * kg.ne + t) * N + src];
+      const uint64_t *kbp = key + 2 * j * krow + (size_t)mi * N;
+      f(j, x, kbp[pos], kbp[krow + pos]);
+    }
+  };
+  uint64_t r0, r1;
+  if (m.qd != 0.0) {
+    const ArF ar{m.qd, m.qid};
+    double s0 = 0.0, s1 = 0.0;
+    digits([&](uint32_t j, uint64_t x, uint64_t k0, uint64_t k1) {
+      const double xd = ar.load(x);  // products within 0.7 q, sums within 6.1 q
+      s0 += ar.mul2(xd, ArF::raw(k0));
+      s1 += ar.mul2(xd, ArF::raw(k1));
+      if ((j & 7) == 7) {
+        s0 = ar.reduce(s0);
+        s1 = ar.reduce(s1);
+      }
+    });
+    r0 = ar.canon(s0);
+    r1 = ar.canon(s1);
+  } else {
+    u128 s0, s1;
+    s0.lo = s0.hi = s1.lo = s1.hi = 0;
+    digits([&](uint32_t, uint64_t x, uint64_t k0, uint64_t k1) {
+      mac_wide(s0, x, k0);
+      mac_wide(s1, x, k1);
+    });
+    r0 = redc(s0, m.q, m.qinv);
+    r1 = redc(s1, m.q, m.qinv);
+  }
+  slot[((size_t)kg.off_acc + t) * N + pos] = r0;
+  slot[((size_t)kg.off_acc + kg.ne + t) * N + pos] = r1;
 }
 
 KsGeom make_geom(const hck_context *ctx, uint32_t level) {
@@ -547,22 +805,15 @@ int ks_modup(hck_context *ctx, const KsBatch &kb, const KsGeom &kg, uint64_t *ws
   constexpr double N = (double)(1 << LOGN);
   using GA = Pass<A, LOGN, true>;
   using GB = Pass<B, LOGN, false>;
-  const uint32_t L = kg.L, nm = kg.nm, alpha = kg.alpha, nq = kg.nq, ne = kg.ne, nb = kb.n;
-  const uint32_t level = kg.level;
+  const uint32_t nq = kg.nq, nb = kb.n, level = kg.level;
   int rc;
   double copies = 0;   // c0 tiles copied for outputs that alias their input
   for (uint32_t b = 0; b < nb; b++) copies += kb.add0_src[b] ? nq : 0;
   timing_begin(ctx, "ks_intt_gather", dim3(GB::BLOCKS, nb, nq), 16.0 * N * (nq * nb + copies),
                0.5 * N * B * nq * nb);
   k_ks_intt_gather<LOGN><<<dim3(GB::BLOCKS, nb, nq), kNttThreads, 0, ctx->stream>>>(
-      ws, kb, kg, ctx->d_mod, ctx->d_itw, ctx->d_itw_shoup, ctx->d_ittw, ctx->d_ittw_shoup);
+      ws, kb, kg, ctx->d_mod, ctx->d_itn, ctx->split[0].itwist);
   timing_end(ctx);
-  RowScale sc;
-  for (uint32_t i = 0; i < nq; i++) {
-    sc.w[i] = ctx->up_scale[level][i];
-    sc.wp[i] = h_shoup(sc.w[i], ctx->mods[i]);
-    sc.add[i] = 0;
-  }
   {
     LimbMap m;
     m.n = nq * nb;
@@ -571,122 +822,56 @@ int ks_modup(hck_context *ctx, const KsBatch &kb, const KsGeom &kg, uint64_t *ws
         m.row[b * nq + i] = (uint16_t)(b * kg.slot_rows + i);
         m.mod[b * nq + i] = (uint8_t)i;
       }
-    if ((rc = ntt_pass(ctx, ws, m, true, true, &sc, (int)nq))) return rc;
+    const RowFactors sc{ctx->d_up_rows + ((size_t)level * kg.L << A), nullptr, nq, false};
+    if ((rc = ntt_pass(ctx, ws, m, true, true, &sc))) return rc;
   }
-  struct Row {
-    uint16_t row, src;
-    uint8_t mod, digit;
-    uint32_t na;
-  };
-  std::vector<Row> ext_rows;
-  for (uint32_t b = 0; b < nb; b++)
-    for (uint32_t j = 0; j < kg.dnum; j++) {
-      const uint32_t lo = j * alpha;
-      if (lo >= nq) break;
-      const uint32_t hi = std::min(lo + alpha, nq);
-      for (uint32_t t = 0; t < ne; t++) {
-        if (t >= lo && t < hi) continue;
-        Row rw;
-        rw.row = (uint16_t)(b * kg.slot_rows + kg.off_ext + j * ne + t);
-        rw.src = (uint16_t)(b * kg.slot_rows + lo);
-        rw.mod = (uint8_t)(t < nq ? t : L + (t - nq));
-        rw.digit = (uint8_t)j;
-        rw.na = hi - lo;
-        ext_rows.push_back(rw);
-      }
-    }
-  const uint64_t *up_conv = ctx->d_up_conv + (size_t)level * kg.dnum * alpha * nm;
   // in a launch large enough to fill the chip at half the workgroups,
-  // consecutive targets of one digit share a workgroup (one read of the
-  // digit's limbs for both); small launches keep one target per workgroup
-  // and the kernel's lower register count
-  const bool paired = ext_rows.size() * GA::BLOCKS >= kPairMinBlocks;
-  std::vector<std::pair<size_t, size_t>> groups;  // (first row, second row or SIZE_MAX)
-  for (size_t i = 0; i < ext_rows.size();) {
-    const bool pair = paired && i + 1 < ext_rows.size() &&
-                      ext_rows[i + 1].src == ext_rows[i].src &&
-                      ext_rows[i + 1].digit == ext_rows[i].digit;
-    groups.push_back({i, pair ? i + 1 : SIZE_MAX});
-    i += pair ? 2 : 1;
+  // consecutive targets of one digit and arithmetic share a workgroup (one
+  // read of the digit's limbs for both); small launches keep one target per
+  // workgroup and the kernel's lower register count
+  const uint32_t targets = ctx->groups[0][level].second;
+  const bool paired = (size_t)targets * nb * GA::BLOCKS >= kPairMinBlocks;
+  const auto gr = ctx->groups[paired][level];
+  const ConvC *up_conv = ctx->d_up_conv + (size_t)level * kg.dnum * (kg.alpha + 1) * kg.nm;
+  // algorithmic bytes: every digit limb is read once (the targets sharing it
+  // re-read it from cache), every output written
+  double macs = 0;
+  for (uint32_t lo = 0; lo < nq; lo += kg.alpha) {
+    const double na = std::min(kg.alpha, nq - lo);
+    macs += na * (kg.ne - na);
   }
-  for (size_t s = 0; s < groups.size(); s += kMaxRows) {
-    ModUpRows mr;
-    mr.n = (uint32_t)std::min(groups.size() - s, (size_t)kMaxRows);
-    // algorithmic bytes: every digit limb a launch converts is read once
-    // (the targets sharing it re-read it from cache), every output written
-    double srcs = 0, outs = 0, macs = 0;
-    std::vector<uint16_t> seen;
-    for (uint32_t k = 0; k < mr.n; k++) {
-      const Row &rw = ext_rows[groups[s + k].first];
-      if (std::find(seen.begin(), seen.end(), rw.src) == seen.end()) {
-        seen.push_back(rw.src);
-        srcs += rw.na;
-      }
-      mr.row[k] = rw.row;
-      mr.src[k] = rw.src;
-      mr.mod[k] = rw.mod;
-      mr.digit[k] = rw.digit;
-      mr.row2[k] = kNoRow;
-      mr.mod2[k] = rw.mod;
-      outs += 1;
-      macs += rw.na;
-      if (groups[s + k].second != SIZE_MAX) {
-        const Row &r2 = ext_rows[groups[s + k].second];
-        mr.row2[k] = r2.row;
-        mr.mod2[k] = r2.mod;
-        outs += 1;
-        macs += rw.na;
-      }
-    }
-    timing_begin(ctx, "ks_modup_strided", dim3(GA::BLOCKS, mr.n), 8.0 * N * (srcs + outs),
-                 N * (macs + 0.5 * A * outs));
-    const dim3 grid(GA::BLOCKS, mr.n);
-    if (paired && ctx->bconv30)
-      k_modup_strided<LOGN, true, true><<<grid, kNttThreads, 0, ctx->stream>>>(
-          ws, mr, up_conv, kg, ctx->d_mod, ctx->d_tw, ctx->d_tw_shoup);
-    else if (paired)
-      k_modup_strided<LOGN, true, false><<<grid, kNttThreads, 0, ctx->stream>>>(
-          ws, mr, up_conv, kg, ctx->d_mod, ctx->d_tw, ctx->d_tw_shoup);
-    else if (ctx->bconv30)
-      k_modup_strided<LOGN, false, true><<<grid, kNttThreads, 0, ctx->stream>>>(
-          ws, mr, up_conv, kg, ctx->d_mod, ctx->d_tw, ctx->d_tw_shoup);
-    else
-      k_modup_strided<LOGN, false, false><<<grid, kNttThreads, 0, ctx->stream>>>(
-          ws, mr, up_conv, kg, ctx->d_mod, ctx->d_tw, ctx->d_tw_shoup);
-    timing_end(ctx);
-  }
+  const dim3 grid(GA::BLOCKS, gr.second, nb);
+  timing_begin(ctx, "ks_modup_strided", grid, 8.0 * N * nb * (nq + targets),
+               N * nb * (macs + 0.5 * A * targets));
+  const ConvGroup *groups = ctx->d_groups + gr.first;
+  const bool s30 = ctx->bconv30 && ctx->conv_f;
+  auto launch = [&](auto kernel, int threads) {
+    kernel<<<grid, threads, 0, ctx->stream>>>(ws, groups, up_conv, kg, ctx->d_mod, ctx->d_tw);
+  };
+  if (!s30)
+    launch(paired ? k_modup_strided<LOGN, true, false> : k_modup_strided<LOGN, false, false>,
+           kNttThreads);
+  else if (paired)
+    launch(k_modup_strided<LOGN, true, true>, kNttThreads);
+  else
+    launch(k_modup_strided<LOGN, false, true>, ConvPass<LOGN, false, true>::THREADS);
+  timing_end(ctx);
   HCK_HIP(ctx, hipGetLastError());
   return HCK_OK;
 }
 
-// K6 launch: the basis conversion on 30-bit halves where every modulus is
-// below 2^60, on whole words otherwise
-template <int LOGN, bool PAIR>
-void launch_moddown_strided(hck_context *ctx, uint64_t *ws, const KsGeom &kg, uint32_t per,
-                            uint32_t nb) {
-  using GA = Pass<split_a(LOGN), LOGN, true>;
-  const dim3 grid(GA::BLOCKS, 2 * per, nb);
-  if (ctx->bconv30)
-    k_moddown_strided<LOGN, PAIR, true><<<grid, kNttThreads, 0, ctx->stream>>>(
-        ws, ctx->d_down_conv, ctx->d_down_hneg, kg, ctx->d_mod, ctx->d_tw, ctx->d_tw_shoup);
-  else
-    k_moddown_strided<LOGN, PAIR, false><<<grid, kNttThreads, 0, ctx->stream>>>(
-        ws, ctx->d_down_conv, ctx->d_down_hneg, kg, ctx->d_mod, ctx->d_tw, ctx->d_tw_shoup);
-}
-
-// K5-K7 for batch slots 0..nb-1 (ModDown of each slot's acc rows)
+// K5 and K6 for batch slots 0..nb-1: each slot's special accumulators
+// (canonical: fully reduced words, else as k_ks_contig_inner leaves them)
+// converted to the Q limbs (conv rows, strided pass done)
 template <int LOGN>
-int ks_moddown(hck_context *ctx, const KsBatch &kb, const KsGeom &kg, uint64_t *ws,
-               bool special_contig_done) {
-  constexpr int A = split_a(LOGN), B = split_b(LOGN);
+int ks_down_conv(hck_context *ctx, uint32_t nb, const KsGeom &kg, uint64_t *ws, bool canonical) {
+  constexpr int A = split_a(LOGN);
   constexpr double N = (double)(1 << LOGN);
   using GA = Pass<A, LOGN, true>;
-  using GB = Pass<B, LOGN, false>;
-  const uint32_t L = kg.L, K = kg.K, nq = kg.nq, ne = kg.ne, nb = kb.n;
+  const uint32_t L = kg.L, K = kg.K, nq = kg.nq, ne = kg.ne;
   int rc;
   {
     LimbMap mp;
-    RowScale sp;
     mp.n = 2 * K * nb;
     for (uint32_t b = 0; b < nb; b++)
       for (uint32_t p = 0; p < 2; p++)
@@ -695,42 +880,103 @@ int ks_moddown(hck_context *ctx, const KsBatch &kb, const KsGeom &kg, uint64_t *
           mp.row[r] = (uint16_t)(b * kg.slot_rows + kg.off_acc + p * ne + nq + k);
           mp.mod[r] = (uint8_t)(L + k);
         }
-    for (uint32_t p = 0; p < 2; p++)
-      for (uint32_t k = 0; k < K; k++) {
-        sp.w[p * K + k] = ctx->down_scale[k];
-        sp.wp[p * K + k] = h_shoup(ctx->down_scale[k], ctx->mods[L + k]);
-        sp.add[p * K + k] = ctx->down_add[k];
-      }
-    // the inverse contiguous pass of the special limbs is fused into the
-    // inner-product kernel's epilogue, except on the hoisted path
-    if (!special_contig_done && (rc = ntt_pass(ctx, ws, mp, true, false, nullptr))) return rc;
-    if ((rc = ntt_pass(ctx, ws, mp, true, true, &sp, (int)(2 * K)))) return rc;
+    const RowFactors sc{ctx->d_down_rows, ctx->d_down_add, K, canonical};
+    if ((rc = ntt_pass(ctx, ws, mp, true, true, &sc))) return rc;
   }
   // in a launch large enough to fill the chip at half the workgroups, the K
   // special limbs are read once per pair of target limbs
   const bool paired = (size_t)2 * nq * nb * GA::BLOCKS >= kPairMinBlocks;
-  const uint32_t per = paired ? (nq + 1) / 2 : nq;
+  const auto gr = ctx->down_groups[paired][kg.level];
+  const ConvGroup *groups = ctx->d_groups + gr.first;
+  const dim3 grid(GA::BLOCKS, 2 * gr.second, nb);
   // algorithmic bytes: each output's K special limbs read once, its target
   // limbs written
-  timing_begin(ctx, "ks_moddown_strided", dim3(GA::BLOCKS, 2 * per, nb),
-               8.0 * N * (K + nq) * 2 * nb, N * (K + 0.5 * A) * 2 * nq * nb);
-  if (paired)
-    launch_moddown_strided<LOGN, true>(ctx, ws, kg, per, nb);
+  timing_begin(ctx, "ks_moddown_strided", grid, 8.0 * N * (K + nq) * 2 * nb,
+               N * (K + 0.5 * A) * 2 * nq * nb);
+  const bool s30 = ctx->bconv30 && ctx->conv_f;
+  auto launch = [&](auto kernel, int threads) {
+    kernel<<<grid, threads, 0, ctx->stream>>>(ws, ctx->d_down_conv, ctx->d_down_hneg, groups, kg,
+                                              ctx->d_mod, ctx->d_tw);
+  };
+  if (!s30)
+    launch(paired ? k_moddown_strided<LOGN, true, false> : k_moddown_strided<LOGN, false, false>,
+           kNttThreads);
+  else if (paired)
+    launch(k_moddown_strided<LOGN, true, true>, kNttThreads);
   else
-    launch_moddown_strided<LOGN, false>(ctx, ws, kg, per, nb);
+    launch(k_moddown_strided<LOGN, false, true>, ConvPass<LOGN, false, true>::THREADS);
   timing_end(ctx);
-  RowScale pinv;
-  for (uint32_t i = 0; i < nq; i++) {
-    pinv.w[i] = ctx->pinv[i];
-    pinv.wp[i] = h_shoup(ctx->pinv[i], ctx->mods[i]);
-    pinv.add[i] = 0;
+  HCK_HIP(ctx, hipGetLastError());
+  return HCK_OK;
+}
+
+// K4 over limbs [first, first + limbs) of the list special limbs, Q limbs
+template <int LOGN, bool TAIL>
+void launch_contig_inner(hck_context *ctx, const KsBatch &kb, const KsGeom &kg, uint64_t *ws,
+                         uint32_t first, uint32_t limbs, bool canonical) {
+  constexpr int B = split_b(LOGN);
+  constexpr double N = (double)(1 << LOGN);
+  using GB = Pass<B, LOGN, false>;
+  const uint32_t nq = kg.nq, nb = kb.n, alpha = kg.alpha;
+  const double digits = (double)((nq + alpha - 1) / alpha);
+  const double q_limbs = first + limbs > kg.K ? first + limbs - std::max(first, kg.K) : 0;
+  const double p_limbs = limbs - q_limbs;
+  double keys = 0;  // distinct keys in the batch
+  double adds = 0;
+  for (uint32_t b = 0; b < nb; b++) {
+    bool seen = false;
+    for (uint32_t k = 0; k < b; k++) seen = seen || kb.key[k] == kb.key[b];
+    keys += seen ? 0 : 1;
+    if (TAIL) adds += (kb.add0[b] ? nq : 0) + (kb.add1[b] ? nq : 0);
   }
+  const double ext = nb * (digits * limbs - q_limbs);  // transformed digit limbs
+  // accumulators written, or (tail) conv read and outputs written
+  const double io = nb * (TAIL ? 4.0 : 2.0) * limbs;
+  timing_begin(ctx, TAIL ? "ks_inner_tail" : "ks_contig_inner", dim3(GB::BLOCKS, nb, limbs),
+               8.0 * N * (ext + nb * q_limbs + io + adds + 2 * digits * limbs * keys),
+               N * (0.5 * B * (ext + 2.0 * nb * (TAIL ? q_limbs : p_limbs)) +
+                    2 * digits * limbs * nb + (TAIL ? 2.0 * nb * q_limbs : 0.0)));
+  const dim3 grid(GB::BLOCKS, nb, limbs);
+  auto launch = [&](auto kernel, int threads) {
+    kernel<<<grid, threads, 0, ctx->stream>>>(ws, kb, kg, first, canonical ? 1 : 0, ctx->d_mod,
+                                              ctx->d_tw, ctx->split[0].twist, ctx->d_itn,
+                                              ctx->split[0].itwist, ctx->d_pinv);
+  };
+  if ((size_t)grid.x * grid.y * grid.z <= kSplitMaxBlocks)
+    launch(k_ks_contig_inner<LOGN, TAIL, true>, 2 * kNttThreads);
+  else
+    launch(k_ks_contig_inner<LOGN, TAIL, false>, kNttThreads);
+  timing_end(ctx);
+}
+
+// K5-K7 for batch slots 0..nb-1 with every accumulator (fully reduced) in
+// the slots' acc rows; special_contig_done: the special rows have been
+// through the inverse contiguous pass
+template <int LOGN>
+int ks_moddown(hck_context *ctx, const KsBatch &kb, const KsGeom &kg, uint64_t *ws,
+               bool special_contig_done) {
+  constexpr int B = split_b(LOGN);
+  constexpr double N = (double)(1 << LOGN);
+  using GB = Pass<B, LOGN, false>;
+  const uint32_t nq = kg.nq, nb = kb.n;
+  int rc;
+  if (!special_contig_done) {
+    LimbMap mp;
+    mp.n = 2 * kg.K * nb;
+    for (uint32_t r = 0; r < mp.n; r++) {
+      const uint32_t b = r / (2 * kg.K), p = r / kg.K % 2, k = r % kg.K;
+      mp.row[r] = (uint16_t)(b * kg.slot_rows + kg.off_acc + p * kg.ne + nq + k);
+      mp.mod[r] = (uint8_t)(kg.L + k);
+    }
+    if ((rc = ntt_pass(ctx, ws, mp, true, false, nullptr))) return rc;
+  }
+  if ((rc = ks_down_conv<LOGN>(ctx, nb, kg, ws, special_contig_done))) return rc;
   double adds = 0;
   for (uint32_t b = 0; b < nb; b++) adds += (kb.add0[b] ? nq : 0) + (kb.add1[b] ? nq : 0);
   timing_begin(ctx, "ks_moddown_tail", dim3(GB::BLOCKS, nb, 2 * nq),
                8.0 * N * (3.0 * 2 * nq * nb + adds), N * (0.5 * B + 1) * 2 * nq * nb);
   k_moddown_contig_tail<LOGN><<<dim3(GB::BLOCKS, nb, 2 * nq), kNttThreads, 0, ctx->stream>>>(
-      ws, kb, pinv, kg, ctx->d_mod, ctx->d_tw, ctx->d_tw_shoup, ctx->d_ttw, ctx->d_ttw_shoup);
+      ws, kb, ctx->d_pinv, kg, ctx->d_mod, ctx->d_tw, ctx->split[0].twist);
   timing_end(ctx);
   HCK_HIP(ctx, hipGetLastError());
   return HCK_OK;
@@ -738,29 +984,14 @@ int ks_moddown(hck_context *ctx, const KsBatch &kb, const KsGeom &kg, uint64_t *
 
 template <int LOGN>
 int ks_run(hck_context *ctx, const KsBatch &kb, uint32_t level, uint64_t *ws) {
-  constexpr int B = split_b(LOGN);
-  constexpr double N = (double)(1 << LOGN);
-  using GB = Pass<B, LOGN, false>;
   const KsGeom kg = make_geom(ctx, level);
-  const uint32_t nq = kg.nq, ne = kg.ne, nb = kb.n, alpha = kg.alpha;
   int rc;
   if ((rc = ks_modup<LOGN>(ctx, kb, kg, ws))) return rc;
-  const double digits = (double)((nq + alpha - 1) / alpha);
-  const double ext_limbs = nb * (digits * ne - nq);
-  double keys = 0;  // distinct keys in the batch
-  for (uint32_t b = 0; b < nb; b++) {
-    bool seen = false;
-    for (uint32_t k = 0; k < b; k++) seen = seen || kb.key[k] == kb.key[b];
-    keys += seen ? 0 : 1;
-  }
-  timing_begin(ctx, "ks_contig_inner", dim3(GB::BLOCKS, nb, ne),
-               8.0 * N * (ext_limbs + nb * (nq + 2.0 * ne) + 2 * digits * ne * keys),
-               N * (0.5 * B * (ext_limbs + 2.0 * kg.K * nb) + 2 * digits * ne * nb));
-  k_ks_contig_inner<LOGN><<<dim3(GB::BLOCKS, nb, ne), kNttThreads, 0, ctx->stream>>>(
-      ws, kb, kg, ctx->d_mod, ctx->d_tw, ctx->d_tw_shoup, ctx->d_ttw, ctx->d_ttw_shoup,
-      ctx->d_itw, ctx->d_itw_shoup, ctx->d_ittw, ctx->d_ittw_shoup);
-  timing_end(ctx);
-  return ks_moddown<LOGN>(ctx, kb, kg, ws, true);
+  launch_contig_inner<LOGN, false>(ctx, kb, kg, ws, 0, kg.K, false);
+  if ((rc = ks_down_conv<LOGN>(ctx, kb.n, kg, ws, false))) return rc;
+  launch_contig_inner<LOGN, true>(ctx, kb, kg, ws, kg.K, kg.nq, false);
+  HCK_HIP(ctx, hipGetLastError());
+  return HCK_OK;
 }
 
 template <int LOGN>
@@ -809,12 +1040,12 @@ int ks_hoisted(hck_context *ctx, const uint64_t *c0, const uint64_t *c1, uint32_
       kb.out1[b] = out1[s + b];
       kb.add0[b] = c0;
       kb.add1[b] = nullptr;
-      timing_begin(ctx, "ks_inner_gather", dim3((1 << LOGN) / 256, ne),
-                   8.0 * N * ne * (3 * digits + 2), 2 * digits * N * ne);
-      k_ks_inner_gather<LOGN><<<dim3((1 << LOGN) / 256, ne), 256, 0, ctx->stream>>>(
-          ws_ks(ctx), c1, galois[s + b], b, keys[s + b]->data, kg, ctx->d_mod);
-      timing_end(ctx);
     }
+    timing_begin(ctx, "ks_inner_gather", dim3((1 << LOGN) / 256, kb.n, ne),
+                 8.0 * N * ne * (digits + (2 * digits + 2) * kb.n), 2 * digits * N * ne * kb.n);
+    k_ks_inner_gather<LOGN><<<dim3((1 << LOGN) / 256, kb.n, ne), 256, 0, ctx->stream>>>(
+        ws_ks(ctx), c1, kb, kg, ctx->d_mod);
+    timing_end(ctx);
     if ((rc = ks_moddown<LOGN>(ctx, kb, kg, ws_ks(ctx), false))) return rc;
   }
   HCK_HIP(ctx, hipGetLastError());
@@ -825,22 +1056,12 @@ int ks_hoisted(hck_context *ctx, const uint64_t *c0, const uint64_t *c1, uint32_
 template <int LOGN>
 int ks_pq(hck_context *ctx, const KsBatch &kb, uint32_t level, uint64_t *const *pq,
           const bool *first) {
-  constexpr int B = split_b(LOGN);
-  constexpr double N = (double)(1 << LOGN);
-  using GB = Pass<B, LOGN, false>;
+  constexpr size_t N = 1 << LOGN;
   const KsGeom kg = make_geom(ctx, level);
-  const uint32_t nq = kg.nq, ne = kg.ne, nb = kb.n, alpha = kg.alpha;
+  const uint32_t nq = kg.nq, ne = kg.ne, nb = kb.n;
   int rc;
   if ((rc = ks_modup<LOGN>(ctx, kb, kg, ws_ks(ctx)))) return rc;
-  const double digits = (double)((nq + alpha - 1) / alpha);
-  const double ext_limbs = nb * (digits * ne - nq);
-  timing_begin(ctx, "ks_contig_inner", dim3(GB::BLOCKS, nb, ne),
-               8.0 * N * (ext_limbs + nb * (nq + 2.0 * ne) + 2 * digits * ne * nb),
-               N * (0.5 * B * (ext_limbs + 2.0 * kg.K * nb) + 2 * digits * ne * nb));
-  k_ks_contig_inner<LOGN><<<dim3(GB::BLOCKS, nb, ne), kNttThreads, 0, ctx->stream>>>(
-      ws_ks(ctx), kb, kg, ctx->d_mod, ctx->d_tw, ctx->d_tw_shoup, ctx->d_ttw,
-      ctx->d_ttw_shoup, ctx->d_itw, ctx->d_itw_shoup, ctx->d_ittw, ctx->d_ittw_shoup);
-  timing_end(ctx);
+  launch_contig_inner<LOGN, false>(ctx, kb, kg, ws_ks(ctx), 0, ne, true);
   HCK_HIP(ctx, hipGetLastError());
   LimbMap rows;
   rows.n = 2 * ne;
@@ -857,7 +1078,7 @@ int ks_pq(hck_context *ctx, const KsBatch &kb, uint32_t level, uint64_t *const *
     for (uint32_t k = b; k < nb; k++)
       if (pq[k] == pq[b]) {
         done[k] = true;
-        in.push_back(ws_ks(ctx) + ((size_t)k * kg.slot_rows + kg.off_acc) * (size_t)N);
+        in.push_back(ws_ks(ctx) + ((size_t)k * kg.slot_rows + kg.off_acc) * N);
       }
     if ((rc = launch_sum_many(ctx, pq[b], in.data(), (uint32_t)in.size(), rows))) return rc;
   }
@@ -877,118 +1098,31 @@ int md_pq(hck_context *ctx, const KsBatch &kb, uint32_t level, const uint64_t *c
 
 }  // namespace
 
-// Batches grow where each slot is small (low levels), so that a launch still
-// fills the chip; at high levels 8 slots of 24 limbs already do, and larger
-// batches measured slower there (more data between the passes of a batch).
-uint32_t ks_batch_fit(const hck_context *ctx, uint32_t level) {
-  const uint32_t by_rows = (uint32_t)kMaxRows / std::max<uint32_t>(level + 1, 2 * ctx->K);
-  return std::max<uint32_t>(1, std::min(ks_slots(ctx), by_rows));
+template <int LOGN>
+int KsRing<LOGN>::run(hck_context *ctx, const KsBatch &kb, uint32_t level, uint64_t *ws) {
+  return ks_run<LOGN>(ctx, kb, level, ws);
 }
 
-uint32_t ks_batch_limit(const hck_context *ctx, uint32_t level) {
-  const uint32_t fit = ks_batch_fit(ctx, level);
-  if (level < (uint32_t)HCK_MAX_LIMBS && ctx->ks_cap[level])
-    return std::min<uint32_t>(fit, ctx->ks_cap[level]);
-  return std::min<uint32_t>(fit, std::max<uint32_t>(1, 192 / (level + 1)));
+template <int LOGN>
+int KsRing<LOGN>::hoisted(hck_context *ctx, const uint64_t *c0, const uint64_t *c1,
+                          uint32_t level, const uint32_t *galois,
+                          const hck_switch_key *const *keys, uint32_t n, uint64_t *const *out0,
+                          uint64_t *const *out1) {
+  return ks_hoisted<LOGN>(ctx, c0, c1, level, galois, keys, n, out0, out1);
 }
 
-int keyswitch_batch(hck_context *ctx, const KsBatch &kb, uint32_t level) {
-  if (kb.n == 0) return HCK_OK;
-  if (kb.n > ks_slots(ctx)) return set_error(HCK_EINVAL, "batch too large");
-  int rc = ensure_workspace(ctx, ws_words_needed(ctx));
-  if (rc) return rc;
-  return keyswitch_batch_ws(ctx, kb, level, ws_ks(ctx));
+template <int LOGN>
+int KsRing<LOGN>::pq(hck_context *ctx, const KsBatch &kb, uint32_t level, uint64_t *const *pq,
+                     const bool *first) {
+  return ks_pq<LOGN>(ctx, kb, level, pq, first);
 }
 
-int keyswitch_batch_ws(hck_context *ctx, const KsBatch &kb, uint32_t level, uint64_t *ws) {
-  if (kb.n == 0) return HCK_OK;
-  if (level + 1 > (uint32_t)kMaxLimbs || (level + 1) * kb.n > (uint32_t)kMaxRows ||
-      2 * ctx->K * kb.n > (uint32_t)kMaxRows)
-    return set_error(HCK_EINVAL, "level too high for one batched launch");
-  switch (ctx->log_n) {
-    case 11: return ks_run<11>(ctx, kb, level, ws);
-    case 12: return ks_run<12>(ctx, kb, level, ws);
-    case 13: return ks_run<13>(ctx, kb, level, ws);
-    case 14: return ks_run<14>(ctx, kb, level, ws);
-    case 15: return ks_run<15>(ctx, kb, level, ws);
-    case 16: return ks_run<16>(ctx, kb, level, ws);
-    case 17: return ks_run<17>(ctx, kb, level, ws);
-    default: return set_error(HCK_EPARAMS, "unsupported ring degree");
-  }
+template <int LOGN>
+int KsRing<LOGN>::md(hck_context *ctx, const KsBatch &kb, uint32_t level,
+                     const uint64_t *const *pq) {
+  return md_pq<LOGN>(ctx, kb, level, pq);
 }
 
-int keyswitch_core(hck_context *ctx, const uint64_t *d, uint32_t galois, uint32_t level,
-                   const hck_switch_key *key, uint64_t *out0, uint64_t *out1, const uint64_t *add0,
-                   const uint64_t *add1) {
-  KsBatch kb;
-  kb.n = 1;
-  kb.key[0] = key->data;
-  kb.galois[0] = galois;
-  kb.d[0] = d;
-  kb.out0[0] = out0;
-  kb.out1[0] = out1;
-  kb.add0[0] = add0;
-  kb.add1[0] = add1;
-  return keyswitch_batch(ctx, kb, level);
-}
-
-int keyswitch_hoisted(hck_context *ctx, const uint64_t *c0, const uint64_t *c1, uint32_t level,
-                      const uint32_t *galois, const hck_switch_key *const *keys, uint32_t n,
-                      uint64_t *const *out0, uint64_t *const *out1) {
-  if (n == 0) return HCK_OK;
-  int rc = ensure_workspace(ctx, ws_words_needed(ctx));
-  if (rc) return rc;
-  if (level + 1 > (uint32_t)kMaxLimbs || 2 * ctx->K > (uint32_t)kMaxRows)
-    return set_error(HCK_EINVAL, "level too high for one batched launch");
-  switch (ctx->log_n) {
-    case 11: return ks_hoisted<11>(ctx, c0, c1, level, galois, keys, n, out0, out1);
-    case 12: return ks_hoisted<12>(ctx, c0, c1, level, galois, keys, n, out0, out1);
-    case 13: return ks_hoisted<13>(ctx, c0, c1, level, galois, keys, n, out0, out1);
-    case 14: return ks_hoisted<14>(ctx, c0, c1, level, galois, keys, n, out0, out1);
-    case 15: return ks_hoisted<15>(ctx, c0, c1, level, galois, keys, n, out0, out1);
-    case 16: return ks_hoisted<16>(ctx, c0, c1, level, galois, keys, n, out0, out1);
-    case 17: return ks_hoisted<17>(ctx, c0, c1, level, galois, keys, n, out0, out1);
-    default: return set_error(HCK_EPARAMS, "unsupported ring degree");
-  }
-}
-
-}  // namespace hck
-
-namespace hck {
-
-int keyswitch_pq(hck_context *ctx, const KsBatch &kb, uint32_t level, uint64_t *const *pq,
-                 const bool *first) {
-  if (kb.n == 0) return HCK_OK;
-  if (kb.n > ks_batch_limit(ctx, level)) return set_error(HCK_EINVAL, "batch too large");
-  int rc = ensure_workspace(ctx, ws_words_needed(ctx));
-  if (rc) return rc;
-  switch (ctx->log_n) {
-    case 11: return ks_pq<11>(ctx, kb, level, pq, first);
-    case 12: return ks_pq<12>(ctx, kb, level, pq, first);
-    case 13: return ks_pq<13>(ctx, kb, level, pq, first);
-    case 14: return ks_pq<14>(ctx, kb, level, pq, first);
-    case 15: return ks_pq<15>(ctx, kb, level, pq, first);
-    case 16: return ks_pq<16>(ctx, kb, level, pq, first);
-    case 17: return ks_pq<17>(ctx, kb, level, pq, first);
-    default: return set_error(HCK_EPARAMS, "unsupported ring degree");
-  }
-}
-
-int moddown_pq(hck_context *ctx, const KsBatch &kb, uint32_t level, const uint64_t *const *pq) {
-  if (kb.n == 0) return HCK_OK;
-  if (kb.n > ks_batch_limit(ctx, level)) return set_error(HCK_EINVAL, "batch too large");
-  int rc = ensure_workspace(ctx, ws_words_needed(ctx));
-  if (rc) return rc;
-  switch (ctx->log_n) {
-    case 11: return md_pq<11>(ctx, kb, level, pq);
-    case 12: return md_pq<12>(ctx, kb, level, pq);
-    case 13: return md_pq<13>(ctx, kb, level, pq);
-    case 14: return md_pq<14>(ctx, kb, level, pq);
-    case 15: return md_pq<15>(ctx, kb, level, pq);
-    case 16: return md_pq<16>(ctx, kb, level, pq);
-    case 17: return md_pq<17>(ctx, kb, level, pq);
-    default: return set_error(HCK_EPARAMS, "unsupported ring degree");
-  }
-}
+template struct KsRing<HCK_LOGN>;
 
 }  // namespace hck

@@ -63,6 +63,14 @@ __host__ __device__ __forceinline__ uint64_t shoup_lazy(uint64_t a, uint64_t w, 
   return mul_lo(a, w) - mul_lo(mul_hi(a, wp), q);
 }
 
+// A constant factor modulo q with its companion, for the products of the
+// transforms: moduli in the floating-point range (ModConst::qd) hold the
+// centred factor and its quotient by q as doubles, others the factor in
+// [0, q) and floor(w 2^64 / q).
+struct alignas(16) Tw {
+  uint64_t w, wp;
+};
+
 // A modulus with its negation nq = 2^64 - q.  nq comes from memory, so the
 // compiler cannot see that it is -q and keeps "+ k nq" a multiply-add
 // (v_mad_u64_u32 takes the addend) and "+ nq" one 64-bit add, where "- k q"
@@ -139,6 +147,29 @@ inline uint64_t h_inv64(uint64_t q) {
   uint64_t x = q;  // correct to 3 bits for odd q
   for (int i = 0; i < 6; i++) x *= 2 - q * x;
   return x;
+}
+
+// Moduli whose residues the transforms keep in doubles (ntt_core.h): large
+// enough that a quotient by q stays exact, small enough that 8 q fits 53 bits.
+inline bool h_float_modulus(uint64_t q) {
+  return q >= (1ull << 26) && q < (1ull << 50) + (1ull << 44);
+}
+
+inline uint64_t h_bits(double d) {
+  uint64_t u;
+  __builtin_memcpy(&u, &d, 8);
+  return u;
+}
+
+// w in [0, q) centred about 0.
+inline int64_t h_centred(uint64_t w, uint64_t q) {
+  return w > q / 2 ? (int64_t)w - (int64_t)q : (int64_t)w;
+}
+
+inline Tw h_tw(uint64_t w, uint64_t q) {
+  if (!h_float_modulus(q)) return Tw{w, h_shoup(w, q)};
+  const double c = (double)h_centred(w, q);
+  return Tw{h_bits(c), h_bits(c / (double)q)};
 }
 
 // 2^64 mod q.

@@ -1,0 +1,95 @@
+"""Bit-exact parity where the library's arithmetic changes form: moduli on
+either side of the floating-point range, of 2^60 and of every size in one
+chain, digits of one to sixteen primes, and extreme residues, at rings whose
+passes take each geometry and launches of each size class."""
+import numpy as np
+import pytest
+
+import oracle as O
+import paper_2603_22437_amd as H
+import seeded_inputs as S
+
+pytestmark = pytest.mark.gpu
+
+
+def _primes(two_n, start, count, taken, step):
+    """`count` primes = 1 mod 2N from `start` on, upwards (step 1) or down."""
+    out, x = [], start // two_n * two_n + 1
+    if step > 0 and x < start:
+        x += two_n
+    if step < 0 and x >= start:
+        x -= two_n
+    while len(out) < count:
+        if S.is_prime(x) and x not in taken:
+            out.append(x)
+            taken.add(x)
+        x += step * two_n
+    return out
+
+
+def _params(kind, log_n):
+    two_n, taken = 2 << log_n, set()
+    limit = (1 << 50) + (1 << 44)     # moduli from 2^26 to here run on doubles
+    pick = lambda start, count, step: _primes(two_n, start, count, taken, step)
+    if kind == "edges":     # both sides of every boundary, in one chain
+        q = (pick(1 << 60, 1, -1) + pick(limit, 1, -1) + pick(limit, 1, 1) +
+             pick(1 << 26, 1, 1) + pick(1 << 26, 1, -1) + pick(1 << 45, 1, 1) +
+             pick(1 << 52, 1, 1))
+        p, dnum = pick(1 << 50, 1, -1) + pick(1 << 60, 1, -1) + pick(1 << 58, 1, 1), 3
+    elif kind == "wide":    # moduli up to 2^61 (whole-word conversions)
+        q = pick(1 << 61, 1, -1) + pick(1 << 50, 2, -1) + pick(1 << 60, 1, 1) + pick(1 << 40, 1, 1)
+        p, dnum = pick(1 << 61, 2, -1), 3
+    elif kind == "long":    # one digit of sixteen primes, fifteen special primes
+        q = pick(1 << 60, 1, -1) + pick(1 << 50, 15, -1)
+        p, dnum = pick(1 << 60, 15, -1), 1
+    else:                   # "many": one prime a digit
+        q = pick(1 << 60, 1, -1) + pick(1 << 50, 11, 1)
+        p, dnum = pick(1 << 60, 1, -1), 12
+    return dict(name=f"{kind}/{log_n}", log_n=log_n, n=1 << log_n, q=q, p=p, dnum=dnum,
+                scale=2.0 ** 40)
+
+
+def _residues(mods, n, kind, seed):
+    if kind == "uniform":
+        return S.uniform_residues(mods, n, seed, 2)
+    out = np.empty((2, len(mods), n), dtype=np.uint64)
+    for i, q in enumerate(mods):
+        out[:, i] = q - 1 if kind == "top" else np.where(np.arange(n) % 2, q // 2, q // 2 + 1)
+    return out
+
+
+@pytest.mark.parametrize("kind,log_n", [("edges", 11), ("edges", 14), ("edges", 15), ("edges", 16),
+                                        ("edges", 17), ("wide", 12), ("wide", 15), ("long", 12),
+                                        ("many", 13)])
+def test_mixed_moduli_match_oracle(kind, log_n):
+    prm = _params(kind, log_n)
+    o, ctx = O.Oracle(prm), H.Context.from_params(prm)
+    sk, s_o = ctx.keygen_secret(1), o.keygen_secret(1)
+    step = 3
+    g = o.galois_element(step)
+    gks, gko = ctx.keygen_rotation(sk, [step], 5), {g: o.keygen_galois(s_o, g, 5)}
+    rlk, rlk_o = ctx.keygen_relin(sk, 7), o.keygen_relin(s_o, 7)
+    assert np.array_equal(ctx.switch_key_export(rlk), rlk_o)
+    assert np.array_equal(ctx.switch_key_export(ctx.switch_key_import(rlk_o)), rlk_o)
+    levels = sorted({0, 1, o.L // 2, o.L - 1}) if log_n < 15 else sorted({0, o.L - 1})
+    for level in levels:
+        for i, values in enumerate(("uniform", "top", "middle")):
+            r = _residues(o.qmods(level), o.n, values, 60 + level)
+            ct, ct_o = ctx.ciphertext_import(r, level, 2.0 ** 40), O.Ciphertext(r, level, 2.0 ** 40)
+            same = lambda x, y, what: np.testing.assert_array_equal(
+                ctx.ciphertext_export(x)[0], y.polys, f"{what}, level {level}, {values}")
+            same(ct, ct_o, "import and export")
+            same(ctx.rotate(ct, step, gks), o.rotate(ct_o, step, gko), "rotate")
+            if i:
+                continue
+            many = ctx.rotate_many([ct] * 1 + [ctx.ciphertext_import(r, level, 2.0 ** 40)
+                                               for _ in range(6)], step, gks)
+            for y in many:
+                same(y, o.rotate(ct_o, step, gko), "rotate_many")
+            same(ctx.rotate_hoisted(ct, [step], gks)[0],
+                 o.rotate_hoisted(ct_o, [step], gko)[0], "rotate_hoisted")
+            t, t_o = ctx.mul(ct, ct), o.tensor(ct_o, ct_o)
+            same(ctx.relinearize(t, rlk), o.relinearize(t_o, rlk_o), "relinearize")
+            if level:
+                same(ctx.rescale(ct), o.rescale(ct_o), "rescale")
+                same(ctx.rescale(t), o.rescale(t_o), "rescale of three parts")
