@@ -94,15 +94,14 @@ int apply_galois_keys(hck_context *ctx, const hck_ciphertext *const *a, const ui
       const hck_ciphertext *x = a[s + b];
       hck_ciphertext *y = out[s + b];
       scales[b] = x->scale;
-      // (phi_g(c0), 0) + KeySwitch(phi_g(c1)).  c1 is only read by the
-      // launches before the final one, but c0 is gathered through phi_g by the
-      // final launch while it writes the outputs: an output that aliases this
-      // input gets a copy of c0 to read instead
+      // (phi_g(c0), 0) + KeySwitch(phi_g(c1)).  Both parts are gathered through
+      // phi_g by the final launch while it writes the outputs: an output that
+      // aliases this input gets copies to read instead
       if ((rc = ensure_ct(ctx, y, 2))) return rc;
       const uint64_t *c0 = x->data, *c1 = x->data + ps;
       kb.add0_src[b] = nullptr;
       if (y == x) {
-        // the first launch copies c0 into the workspace for the last one
+        // the first launch makes the copies in the workspace for the last one
         kb.add0_src[b] = x->data;
         c0 = ws_rot(ctx) + (size_t)b * ps;
       }

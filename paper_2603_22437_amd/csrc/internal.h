@@ -432,11 +432,13 @@ uint64_t *ws_pq(hck_context *ctx);    // [kLtOut][2][L+K][N]: extended-basis sum
 // form; slots that share a key read it through the cache):
 // (out0[b], out1[b]) = KeySwitch(phi_g(d[b])) + (phi_g(add0[b]), phi_g(add1[b])).
 // d and the addends are [level+1][N] in evaluation form; g = 1 for no
-// automorphism; null addends are skipped.  out rows must not overlap d; with
-// g != 1 they must not overlap the addends.  An output that aliases its
+// automorphism; null addends are skipped.  out rows must not overlap d (but
+// see add0_src); with g != 1 they must not overlap the addends.  An output that aliases its
 // input's c0 sets add0_src[b] = c0 and add0[b] = a workspace copy of
-// [level+1][N] words: the first launch copies c0 there before the last
-// launch overwrites it (null: add0 is read in place).
+// [level+1][N] words: the first launch copies c0 there, and phi_g(d) into the
+// workspace, before the last launch, which reads both across workgroups,
+// overwrites them (null: add0 and d are read in place, and the outputs must
+// not overlap them).
 struct KsBatch {
   uint32_t n;
   const uint64_t *key[kMaxBatch];

@@ -6,7 +6,8 @@
 // the NTT-domain automorphism X -> X^g (g = 1: no automorphism), so a
 // rotation never materializes phi_g(c):
 //   K1  inverse contiguous pass of phi_g(d) over Q_l -> y          (gather;
-//       also the copy of c0 for an output that aliases its input)
+//       also the copies of c0 and phi_g(d) for an output that aliases its
+//       input)
 //   K2  inverse strided pass, row factors with (Q_j / q_i)^-1      (digit scale)
 //   K3  ModUp: per digit j and target limb t not in D_j, the fast basis
 //       conversion of y's digit limbs computed at load time, then the
@@ -75,12 +76,16 @@ __global__ __launch_bounds__(kNttThreads) void k_ks_intt_gather(
   const int c = G::sub(threadIdx.x), r = G::lane(threadIdx.x);
   const int g = blockIdx.x * G::TR + c;
   if (const uint64_t *c0 = kb.add0_src[b]) {
-    // an output aliasing its input: copy this tile of c0 for the last launch
+    // an output aliasing its input: copy this tile of c0 and of phi_g(d) for
+    // the last launch, which writes the output while other workgroups read
+    // both (phi_g(d) into its digit's own ext row, which the ModUp leaves out)
     uint64_t *cp = const_cast<uint64_t *>(kb.add0[b]);
+    uint64_t *dp = y + ((size_t)kg.off_ext + li / kg.alpha * kg.ne + li) * G::N;
 #pragma unroll
     for (int i = 0; i < P; i++) {
-      const size_t a = roff + G::gaddr(g, G::ipoint(r, i));
-      cp[a] = c0[a];
+      const size_t pos = G::gaddr(g, G::ipoint(r, i));
+      cp[roff + pos] = c0[roff + pos];
+      dp[pos] = d[roff + galois_src((uint32_t)pos, galois, LOGN)];
     }
   }
   with_arith(mc[li], [&](auto ar) {
@@ -501,10 +506,16 @@ __attribute__((amdgpu_waves_per_eu(4))) void k_ks_contig_inner(
       };
       if (t >= lo && t < hi) {
         copy_keys();
+        // phi_g(d), or the first launch's copy of it where the output aliases d
+        const uint64_t *own = d + (size_t)t * G::N;
+        uint32_t gs = galois;
+        if (kb.add0_src[b]) {
+          own = slot + ((size_t)kg.off_ext + j * kg.ne + t) * G::N;
+          gs = 1;
+        }
 #pragma unroll
         for (int i = 0; i < P; i++)
-          x[i] = ar.load(d[(size_t)t * G::N +
-                           galois_src((uint32_t)G::gaddr(g, G::ipoint(r, i)), galois, LOGN)]);
+          x[i] = ar.load(own[galois_src((uint32_t)G::gaddr(g, G::ipoint(r, i)), gs, LOGN)]);
       } else {
         const uint64_t *e = slot + ((size_t)kg.off_ext + j * kg.ne + t) * G::N;
 #pragma unroll
@@ -807,8 +818,8 @@ int ks_modup(hck_context *ctx, const KsBatch &kb, const KsGeom &kg, uint64_t *ws
   using GB = Pass<B, LOGN, false>;
   const uint32_t nq = kg.nq, nb = kb.n, level = kg.level;
   int rc;
-  double copies = 0;   // c0 tiles copied for outputs that alias their input
-  for (uint32_t b = 0; b < nb; b++) copies += kb.add0_src[b] ? nq : 0;
+  double copies = 0;   // c0 and phi_g(d) tiles copied for outputs that alias their input
+  for (uint32_t b = 0; b < nb; b++) copies += kb.add0_src[b] ? 2 * nq : 0;
   timing_begin(ctx, "ks_intt_gather", dim3(GB::BLOCKS, nb, nq), 16.0 * N * (nq * nb + copies),
                0.5 * N * B * nq * nb);
   k_ks_intt_gather<LOGN><<<dim3(GB::BLOCKS, nb, nq), kNttThreads, 0, ctx->stream>>>(

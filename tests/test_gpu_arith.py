@@ -93,3 +93,26 @@ def test_mixed_moduli_match_oracle(kind, log_n):
             if level:
                 same(ctx.rescale(ct), o.rescale(ct_o), "rescale")
                 same(ctx.rescale(t), o.rescale(t_o), "rescale of three parts")
+
+
+@pytest.mark.parametrize("name,level,count", [("tiny", 2, 1), ("mix15", 11, 3), ("mix15", 0, 2),
+                                              ("vital", 23, 1), ("vital", 12, 9)])
+def test_rotations_in_place_match_copies(name, level, count):
+    """A rotation that writes its own input: the last launch reads both parts
+    through the automorphism while other workgroups write them."""
+    prm = S.params(name)
+    ctx = H.Context.from_params(prm)
+    sk = ctx.keygen_secret(1)
+    steps = [1, 7, ctx.n_slots - 1]
+    gks = ctx.keygen_rotation(sk, steps, 5)
+    mods = prm["q"][: level + 1]
+    for rep, step in enumerate(steps):
+        rs = [S.uniform_residues(mods, ctx.n, 100 * rep + i, 2) for i in range(count)]
+        cts = [ctx.ciphertext_import(r, level, prm["scale"]) for r in rs]
+        want = [ctx.ciphertext_export(ctx.rotate(c, step, gks))[0] for c in cts]
+        if count == 1:
+            ctx.rotate(cts[0], step, gks, out=cts[0])
+        else:
+            ctx.rotate_many(cts, step, gks, outs=cts)
+        for c, w in zip(cts, want):
+            np.testing.assert_array_equal(ctx.ciphertext_export(c)[0], w)
