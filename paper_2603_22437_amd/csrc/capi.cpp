@@ -189,9 +189,8 @@ int export_rows(hck_context *ctx, const uint64_t *buf, uint32_t polys, uint32_t 
   uint64_t *tmp = nullptr;
   TRY(dev_alloc(ctx, &tmp, (size_t)polys * nlimbs * n));
   int rc = HCK_OK;
-  for (uint32_t p = 0; p < polys && !rc; p++)
-    rc = launch_copy(ctx, tmp + (size_t)p * nlimbs * n, buf + (size_t)p * rows_per_poly * n,
-                     (size_t)nlimbs * n);
+  rc = launch_copy_polys(ctx, tmp, (size_t)nlimbs * n, buf, (size_t)rows_per_poly * n,
+                         (size_t)nlimbs * n, polys);
   auto rows = poly_rows(polys, nlimbs, nlimbs, 0);
   // modulus of compact row (p, i) is the chain index of limb i (+ mod_base)
   for (auto &r : rows) r.second = (uint8_t)(mod_base + r.first % nlimbs);
@@ -246,7 +245,7 @@ int make_switch_key(hck_context *ctx, const hck_secret_key *sk, const uint64_t *
     if (!rc) rc = embed_small_host(ctx, b, e, poly_rows(1, nm, nm));
     if (!rc) rc = ntt_forward_rows(ctx, b, poly_rows(2, nm, nm));
     // b = e - a s
-    if (!rc) rc = launch_mul_mont(ctx, tmp, ak, sk->data, full, 0);
+    if (!rc) rc = launch_mul_mont(ctx, tmp, ak, sk->data, full);
     if (!rc) rc = launch_addsub(ctx, b, b, tmp, full, 1);
     // + (P mod q_i) s' on the limbs of digit j
     const uint32_t lo = j * ctx->alpha, hi = std::min(L, lo + ctx->alpha);
@@ -315,8 +314,7 @@ int ct_to_host_async(hck_context *ctx, const hck_ciphertext *ct, uint64_t *host)
   uint64_t *tmp = nullptr;
   TRY(dev_alloc(ctx, &tmp, words));
   int rc = HCK_OK;
-  for (uint32_t p = 0; p < ct->size && !rc; p++)
-    rc = launch_copy(ctx, tmp + p * rows * n, ct->data + (size_t)p * ctx->L * n, rows * n);
+  rc = launch_copy_polys(ctx, tmp, rows * n, ct->data, (size_t)ctx->L * n, rows * n, ct->size);
   if (!rc) rc = inverse_rows(ctx, tmp, poly_rows(ct->size, ct->level + 1, ct->level + 1));
   if (!rc) {
     hipError_t e = hipMemcpyAsync(host, tmp, words * 8, hipMemcpyDeviceToHost, ctx->stream);
@@ -443,7 +441,7 @@ int hck_keygen_public(hck_context *ctx, const hck_secret_key *sk, uint64_t seed,
   if (!rc) rc = upload(ctx, ak, a.data(), a.size() * 8);
   if (!rc) rc = embed_small_host(ctx, b, e, poly_rows(1, L, L));
   if (!rc) rc = ntt_forward_rows(ctx, b, poly_rows(2, L, L));
-  if (!rc) rc = launch_mul_mont(ctx, tmp, ak, sk->data, qm, 0);
+  if (!rc) rc = launch_mul_mont(ctx, tmp, ak, sk->data, qm);
   if (!rc) rc = launch_addsub(ctx, b, b, tmp, qm, 1);
   if (!rc) rc = mont_rows(ctx, pk->data, poly_rows(2, L, L), true);
   if (rc) {
@@ -487,7 +485,7 @@ int hck_keygen_relin(hck_context *ctx, const hck_secret_key *sk, uint64_t seed,
     TRY(dev_alloc(ctx, &own, (size_t)(ctx->L + ctx->K) * ctx->n));
     s2 = own;
   }
-  int rc = launch_mul_mont(ctx, s2, sk->data, sk->data, fullmap(ctx), 0);
+  int rc = launch_mul_mont(ctx, s2, sk->data, sk->data, fullmap(ctx));
   if (!rc) rc = make_switch_key(ctx, sk, s2, "rlk", seed, out);
   dev_free(ctx, own);
   if (!rc) track(ctx, *out, release_data<hck_switch_key>);
@@ -680,11 +678,28 @@ int hck_encode_const(hck_context *ctx, double value, double scale, uint32_t leve
   if (level >= ctx->L) return set_error(HCK_ELEVEL, "level beyond the chain");
   const double v = value * scale;
   if (!(std::fabs(v) < 9.2e18)) return set_error(HCK_EINVAL, "constant times scale beyond 2^63");
-  std::vector<int64_t> c(ctx->n, 0);
-  c[0] = (int64_t)std::copysign(std::floor(std::fabs(v) + 0.5), v);  // half away from zero
-  std::vector<uint64_t> res;
-  coeffs_to_residues(ctx, c, level, res);
-  return plaintext_from_rows(ctx, res.data(), level, scale, out);
+  // half away from zero; the constant polynomial's value is the same in every
+  // evaluation slot, so each row is one word, in Montgomery form
+  const int64_t c = (int64_t)std::copysign(std::floor(std::fabs(v) + 0.5), v);
+  RowScale w;
+  for (uint32_t i = 0; i <= level; i++) {
+    const uint64_t q = ctx->mods[i], mag = (uint64_t)(c < 0 ? -c : c) % q;
+    w.w[i] = h_mulmod(c < 0 && mag ? q - mag : mag, h_r64(q), q);
+  }
+  hck_plaintext *pt = new hck_plaintext();
+  pt->ctx = ctx;
+  pt->level = level;
+  pt->scale = scale;
+  int rc = dev_alloc(ctx, &pt->data, (size_t)(level + 1) * ctx->n);
+  if (!rc) rc = launch_fill_rows(ctx, pt->data, level + 1, w);
+  if (rc) {
+    dev_free(ctx, pt->data);
+    delete pt;
+    return rc;
+  }
+  track(ctx, pt, release_data<hck_plaintext>);
+  *out = pt;
+  return HCK_OK;
 }
 
 int hck_encode(hck_context *ctx, const double *re, const double *im, uint32_t n_slots,
@@ -821,7 +836,7 @@ int hck_encrypt_sk(hck_context *ctx, const hck_secret_key *sk, const hck_plainte
   TRY(embed_small_host(ctx, c0, e, poly_rows(1, ctx->L, nq)));
   TRY(ntt_forward_rows(ctx, c0, poly_rows(2, ctx->L, nq)));
   // c0 = e + m - a s
-  TRY(launch_mul_mont(ctx, tmp, c1, sk->data, qm, 0));
+  TRY(launch_mul_mont(ctx, tmp, c1, sk->data, qm));
   TRY(launch_addsub(ctx, c0, c0, tmp, qm, 1));
   TRY(launch_copy(ctx, tmp, pt->data, (size_t)nq * n));
   TRY(launch_to_mont(ctx, tmp, qm, false));
@@ -855,8 +870,8 @@ int hck_encrypt_pk(hck_context *ctx, const hck_public_key *pk, const hck_plainte
   TRY(embed_small_host(ctx, c1, e1, poly_rows(1, ctx->L, nq)));
   TRY(ntt_forward_rows(ctx, c0, poly_rows(2, ctx->L, nq)));
   TRY(ntt_forward_rows(ctx, vv, poly_rows(1, ctx->L, nq)));
-  TRY(launch_mul_mont(ctx, c0, vv, pk->data, qm, 1));
-  TRY(launch_mul_mont(ctx, c1, vv, pk->data + ps, qm, 1));
+  TRY(launch_mul_mont(ctx, c0, vv, pk->data, qm, true));
+  TRY(launch_mul_mont(ctx, c1, vv, pk->data + ps, qm, true));
   TRY(launch_copy(ctx, tmp, pt->data, (size_t)nq * n));
   TRY(launch_to_mont(ctx, tmp, qm, false));
   TRY(launch_addsub(ctx, c0, c0, tmp, qm, 0));
@@ -885,10 +900,10 @@ int hck_decrypt(hck_context *ctx, const hck_secret_key *sk, const hck_ciphertext
   uint64_t *tmp = ws_tmp(ctx);
   // m = c0 + REDC(c1 s~) (+ REDC(c2 REDC(s~ s~)))
   if (!rc) rc = launch_copy(ctx, pt->data, ct->data, (size_t)nq * n);
-  if (!rc) rc = launch_mul_mont(ctx, pt->data, ct->data + ps, sk->data, qm, 1);
+  if (!rc) rc = launch_mul_mont(ctx, pt->data, ct->data + ps, sk->data, qm, true);
   if (!rc && ct->size == 3) {
-    rc = launch_mul_mont(ctx, tmp, sk->data, sk->data, qm, 0);
-    if (!rc) rc = launch_mul_mont(ctx, pt->data, ct->data + 2 * ps, tmp, qm, 1);
+    rc = launch_mul_mont(ctx, tmp, sk->data, sk->data, qm);
+    if (!rc) rc = launch_mul_mont(ctx, pt->data, ct->data + 2 * ps, tmp, qm, true);
   }
   if (!rc) rc = launch_to_mont(ctx, pt->data, qm, true);
   if (rc) {
@@ -916,6 +931,7 @@ static int addsub_ct(hck_context *ctx, const hck_ciphertext *a, const hck_cipher
   const double scale = a->scale;
   TRY(ensure_ct(ctx, out, size));
   const size_t ps = poly_stride(ctx);
+  // one launch a polynomial: the launch trace's form of this operation
   for (uint32_t p = 0; p < size; p++)
     TRY(launch_addsub(ctx, out->data + p * ps, a->data + p * ps, b->data + p * ps,
                       qmap(ctx, level), op));
@@ -945,18 +961,12 @@ int hck_add_plain(hck_context *ctx, const hck_ciphertext *a, const hck_plaintext
   if (a->size == 0) return set_error(HCK_EINVAL, "empty ciphertext");
   if (pt->level < a->level) return set_error(HCK_ELEVEL, "plaintext level below ciphertext level");
   if (!scales_match(a->scale, pt->scale)) return set_error(HCK_ESCALE, "scales differ");
-  TRY(ensure_workspace(ctx, ws_words_needed(ctx)));
   const uint32_t size = a->size, level = a->level;
   const double scale = a->scale;
   TRY(ensure_ct(ctx, out, size));
-  const size_t n = ctx->n, ps = poly_stride(ctx);
-  uint64_t *tmp = ws_tmp(ctx);
-  const LimbMap qm = qmap(ctx, level);
-  TRY(launch_copy(ctx, tmp, pt->data, (size_t)(level + 1) * n));
-  TRY(launch_to_mont(ctx, tmp, qm, false));
-  TRY(launch_addsub(ctx, out->data, a->data, tmp, qm, 0));
-  for (uint32_t p = 1; p < size; p++)
-    TRY(launch_copy(ctx, out->data + p * ps, a->data + p * ps, (size_t)(level + 1) * n));
+  // (a ciphertext added to itself in place keeps its other polynomials)
+  TRY(launch_add_plain(ctx, out->data, a->data, pt->data, qmap(ctx, level), out == a ? 1 : size,
+                       poly_stride(ctx)));
   out->size = size;
   out->level = level;
   out->scale = scale;
@@ -976,9 +986,7 @@ int hck_mul_plain(hck_context *ctx, const hck_ciphertext *a, const hck_plaintext
   const double scale = a->scale * pt->scale;
   TRY(ensure_ct(ctx, out, size));
   const size_t ps = poly_stride(ctx);
-  for (uint32_t p = 0; p < size; p++)
-    TRY(launch_mul_mont(ctx, out->data + p * ps, a->data + p * ps, pt->data, qmap(ctx, level),
-                        0));
+  TRY(launch_mul_mont(ctx, out->data, a->data, pt->data, qmap(ctx, level), false, size, ps));
   out->size = size;
   out->level = level;
   out->scale = scale;
@@ -998,8 +1006,7 @@ int hck_drop_level(hck_context *ctx, const hck_ciphertext *a, uint32_t level,
   if (out != a) {
     TRY(ensure_ct(ctx, out, size));
     const size_t ps = poly_stride(ctx);
-    for (uint32_t p = 0; p < size; p++)
-      TRY(launch_copy(ctx, out->data + p * ps, a->data + p * ps, (size_t)(level + 1) * ctx->n));
+    TRY(launch_copy_polys(ctx, out->data, ps, a->data, ps, (size_t)(level + 1) * ctx->n, size));
   }
   out->size = size;
   out->level = level;
@@ -1070,18 +1077,9 @@ int hck_rescale(hck_context *ctx, const hck_ciphertext *a, hck_ciphertext *out) 
   const uint32_t size = a->size, level = a->level;
   const double scale = a->scale / (double)ctx->mods[level];
   TRY(ensure_ct(ctx, out, size));
-  const size_t n = ctx->n, ps = poly_stride(ctx);
-  uint64_t *last = ws_tmp(ctx);
-  uint64_t *lift = last + (size_t)size * n;
-  std::vector<std::pair<uint16_t, uint8_t>> lrows;
-  for (uint32_t p = 0; p < size; p++) {
-    TRY(launch_copy(ctx, last + p * n, a->data + p * ps + (size_t)level * n, n));
-    lrows.push_back({(uint16_t)p, (uint8_t)level});
-  }
-  // dropped limb to coefficient form; then per target limb its centred lift,
-  // forward transform and (c_i - t) q_l^-1, in two fused passes
-  TRY(ntt_inverse(ctx, last, make_map(lrows, 0)));
-  TRY(rescale_fused(ctx, out->data, a->data, last, lift, level, size));
+  // dropped limb to coefficient form, per target limb its centred lift,
+  // forward transform and (c_i - t) q_l^-1, in three launches
+  TRY(rescale_fused(ctx, out->data, a->data, ws_tmp(ctx), level, size));
   out->size = size;
   out->level = level - 1;
   out->scale = scale;
@@ -1099,8 +1097,8 @@ int hck_rotate(hck_context *ctx, const hck_ciphertext *a, int32_t step,
     if (a == out) return HCK_OK;
     TRY(ensure_ct(ctx, out, a->size));
     const size_t ps = poly_stride(ctx);
-    for (uint32_t p = 0; p < a->size; p++)
-      TRY(launch_copy(ctx, out->data + p * ps, a->data + p * ps, (size_t)(a->level + 1) * ctx->n));
+    TRY(launch_copy_polys(ctx, out->data, ps, a->data, ps, (size_t)(a->level + 1) * ctx->n,
+                          a->size));
     out->size = a->size;
     out->level = a->level;
     out->scale = a->scale;

@@ -70,7 +70,7 @@ int apply_galois_multi(hck_context *ctx, const hck_ciphertext *const *a, const u
 
 int apply_galois_keys(hck_context *ctx, const hck_ciphertext *const *a, const uint32_t *g,
                       const hck_switch_key *const *keys, uint32_t n,
-                      hck_ciphertext *const *out) {
+                      hck_ciphertext *const *out, const hck_ciphertext *const *sum) {
   if (n == 0) return HCK_OK;
   const uint32_t level = a[0]->level;
   for (uint32_t i = 0; i < n; i++) {
@@ -112,6 +112,10 @@ int apply_galois_keys(hck_context *ctx, const hck_ciphertext *const *a, const ui
       kb.out1[b] = y->data + ps;
       kb.add0[b] = c0;
       kb.add1[b] = nullptr;
+      if (sum) {
+        kb.sum0[b] = sum[s + b]->data;
+        kb.sum1[b] = sum[s + b]->data + ps;
+      }
     }
     if ((rc = keyswitch_batch(ctx, kb, level))) return rc;
     for (uint32_t b = 0; b < kb.n; b++) {

@@ -68,11 +68,18 @@ std::vector<int32_t> plan_steps(const hck_gesture_plan *p) {
 }
 
 int rotsum(hck_context *ctx, hck_ciphertext *c, uint32_t step, uint32_t count,
-           const hck_galois_keys *gks, Scratch &sc) {
-  hck_ciphertext *t = sc.get();
+           const hck_galois_keys *gks) {
   for (uint64_t s = step; s < (uint64_t)step * count; s *= 2) {
-    TRY(hck_rotate(ctx, c, (int32_t)s, gks, t));
-    TRY(hck_add(ctx, c, t, c));
+    if ((int64_t)s % (ctx->n / 2) == 0) {   // the identity: doubles
+      TRY(hck_add(ctx, c, c, c));
+      continue;
+    }
+    const uint32_t g = galois_of_step(ctx, (int32_t)s);
+    auto it = gks->keys.find(g);
+    if (it == gks->keys.end())
+      return set_error(HCK_ENOKEY, "no Galois key for element " + std::to_string(g));
+    const hck_switch_key *key = it->second;
+    TRY(apply_galois_keys(ctx, &c, &g, &key, 1, &c, &c));
   }
   return HCK_OK;
 }
@@ -93,7 +100,7 @@ int dense(hck_context *ctx, const hck_linear_transform *fc, const hck_plaintext 
   TRY(hck_lt_eval(ctx, &x, 1, &fc, &zero, &zero, nullptr, 1, gks, &out, 1,
                   HCK_LT_HOIST_BABY | HCK_LT_HOIST_GIANT));
   TRY(hck_rescale(ctx, out, out));
-  if (sum_count > 1) TRY(rotsum(ctx, out, sum_from, sum_count, gks, sc));
+  if (sum_count > 1) TRY(rotsum(ctx, out, sum_from, sum_count, gks));
   return hck_add_plain(ctx, out, bias, out);
 }
 
@@ -131,12 +138,12 @@ int front_end(hck_context *ctx, const hck_gesture_plan *p, const hck_ciphertext 
   TRY(hck_rescale(ctx, pw, pw));
   TRY(tap(3, pw));
   // K2: gamma = 4, feature = P w
-  hck_ciphertext *p2 = sc.get(), *p4 = sc.get(), *pl = sc.get();
+  hck_ciphertext *p2 = sc.get(), *p4 = sc.get();
   TRY(mul_rs(ctx, pw, pw, rlk, p2, sc));
   TRY(mul_rs(ctx, p2, p2, rlk, p4, sc));
   TRY(tap(4, p4));
-  TRY(hck_drop_level(ctx, pw, p4->level, pl));
-  return mul_rs(ctx, pl, p4, rlk, feat, sc);
+  const hck_ciphertext pl = at_level(pw, p4->level);
+  return mul_rs(ctx, &pl, p4, rlk, feat, sc);
 }
 
 // the FC network with square activations on the accumulated features, which
@@ -286,7 +293,7 @@ int hck_gesture_eval_taps(hck_context *ctx, const hck_gesture_plan *p, const hck
   hck_ciphertext *feat = sc.get();
   TRY(front_end(ctx, p, re, im, rlk, gks, feat, tap));
   // frame accumulation: every block of rd slots ends with the sum of all
-  TRY(rotsum(ctx, feat, rd, t2, gks, sc));
+  TRY(rotsum(ctx, feat, rd, t2, gks));
   TRY(tap(5, feat));
   return fc_tail(ctx, p, feat, rlk, gks, out, tap);
 }
@@ -328,7 +335,7 @@ int hck_gesture_eval_frames(hck_context *ctx, const hck_gesture_plan *p,
   // the frame sum sits in the first block of rd slots; the FC network reads
   // it in every block, as the batched packing leaves it
   const uint32_t rd = p->bins * p->chirps;
-  TRY(rotsum(ctx, acc, rd, (uint32_t)(ctx->n / 2 / rd), gks, sc));
+  TRY(rotsum(ctx, acc, rd, (uint32_t)(ctx->n / 2 / rd), gks));
   return fc_tail(ctx, p, acc, rlk, gks, out, no_tap);
 }
 
@@ -391,7 +398,7 @@ int hck_gesture_cnn_eval(hck_context *ctx, const hck_gesture_cnn_plan *p,
   const uint32_t rd = p->bins * p->chirps, t2 = pow2_at_least(p->frames);
   hck_ciphertext *feat = sc.get(), *u = sc.get(), *v = sc.get();
   TRY(front_end(ctx, &fe, re, im, rlk, gks, feat, no_tap));
-  TRY(rotsum(ctx, feat, rd, t2, gks, sc));
+  TRY(rotsum(ctx, feat, rd, t2, gks));
   TRY(tap(0, feat));
   const uint32_t deg = p->act_degree;
   TRY(apply_lt(ctx, p->conv1, feat, gks, u));
@@ -401,7 +408,7 @@ int hck_gesture_cnn_eval(hck_context *ctx, const hck_gesture_cnn_plan *p,
   TRY(hck_poly_eval(ctx, u, p->act_coeffs, deg, rlk, v));
   TRY(tap(2, v));
   TRY(apply_lt(ctx, p->dense1, v, gks, u));
-  TRY(rotsum(ctx, u, p->hidden, p->c2 * rd / p->hidden, gks, sc));
+  TRY(rotsum(ctx, u, p->hidden, p->c2 * rd / p->hidden, gks));
   TRY(hck_add_plain(ctx, u, p->bias1, u));
   TRY(hck_poly_eval(ctx, u, p->act_coeffs, deg, rlk, v));
   TRY(tap(3, v));

@@ -217,6 +217,17 @@ struct hck_ciphertext {
   double scale = 1.0;
 };
 
+namespace hck {
+// The first level + 1 limbs of a ciphertext, as an input of the calls that
+// follow: a view of its buffer (limbs are stored first to last at a fixed
+// stride), never an output and never kept.
+inline hck_ciphertext at_level(const hck_ciphertext *a, uint32_t level) {
+  hck_ciphertext v = *a;
+  v.level = level;
+  return v;
+}
+}  // namespace hck
+
 struct hck_plaintext {
   hck_context *ctx = nullptr;
   uint64_t *data = nullptr;  // [level+1][N], evaluation domain, Montgomery form
@@ -315,10 +326,10 @@ int ntt_forward(hck_context *ctx, uint64_t *buf, const LimbMap &map);
 // inverse NTT, in place, times N^-1; input and output fully reduced
 int ntt_inverse(hck_context *ctx, uint64_t *buf, const LimbMap &map);
 // Rescale of polys polynomials at `level` (in and out strided by the
-// polynomial stride, out may be in): last holds each polynomial's dropped limb
-// in coefficient form ([0, q_level)), tmp has room for polys x level limbs.
-int rescale_fused(hck_context *ctx, uint64_t *out, const uint64_t *in, const uint64_t *last,
-                  uint64_t *tmp, uint32_t level, uint32_t polys);
+// polynomial stride, out may be in); tmp has room for polys x (level + 1)
+// limbs.
+int rescale_fused(hck_context *ctx, uint64_t *out, const uint64_t *in, uint64_t *tmp,
+                  uint32_t level, uint32_t polys);
 // whether the plain transforms of a ring can run on split a (the default or
 // one step either side), and the tables of split a (null: not built)
 bool ntt_split_available(uint32_t log_n, int a);
@@ -347,8 +358,8 @@ struct NttRing {
   static int ntt_full(hck_context *ctx, uint64_t *buf, const LimbMap &map, bool inverse);
   static int ntt_pass(hck_context *ctx, uint64_t *buf, const LimbMap &map, bool inverse,
                       bool strided, const RowFactors *scale);
-  static int rescale(hck_context *ctx, uint64_t *out, const uint64_t *in, const uint64_t *last,
-                     uint64_t *tmp, uint32_t level, uint32_t polys);
+  static int rescale(hck_context *ctx, uint64_t *out, const uint64_t *in, uint64_t *tmp,
+                     uint32_t level, uint32_t polys);
 };
 struct KsBatch;
 template <int LOGN>
@@ -366,7 +377,12 @@ struct KsRing {
 int launch_key_form(hck_context *ctx, uint64_t *buf, const LimbMap &map, bool to);
 
 int launch_copy(hck_context *ctx, uint64_t *dst, const uint64_t *src, size_t words);
-// out[r] = a[r] (+|-) b[r] for rows in map; op 0 add, 1 sub, 2 negate a
+// the first `words` words (whole limbs) of `polys` polynomials, with the
+// polynomial strides of either side
+int launch_copy_polys(hck_context *ctx, uint64_t *dst, size_t dps, const uint64_t *src, size_t sps,
+                      size_t words, uint32_t polys);
+// row r < rows of out = v.w[r] in every word
+int launch_fill_rows(hck_context *ctx, uint64_t *out, uint32_t rows, const RowScale &v);
 // out = sum of in[0..n_in) mod q over the rows of map (out may be one of the inputs)
 constexpr int kSumInputs = 32;
 int launch_sum_many(hck_context *ctx, uint64_t *out, const uint64_t *const *in, uint32_t n_in,
@@ -378,12 +394,17 @@ int launch_gather_sum(hck_context *ctx, uint64_t *out, const uint64_t *const *in
                       const uint32_t *galois, uint32_t n_in, const LimbMap &map);
 // measured rate of Shoup modular products on this device (T per second)
 int measure_mulmod_rate(hck_context *ctx, double *tera_per_s);
+// out = a + b (op 0) or a - b (op 1) over the rows of map
 int launch_addsub(hck_context *ctx, uint64_t *out, const uint64_t *a, const uint64_t *b,
                   const LimbMap &map, int op);
-// out = [+-] REDC(a * bm) [+ out] (bm in Montgomery form): mode 0 set,
-// 1 add to out, 2 subtract from out, 3 set negated
+// out_0 = a_0 + pt (pt in Montgomery form), out_p = a_p for the others
+int launch_add_plain(hck_context *ctx, uint64_t *out, const uint64_t *a, const uint64_t *pt,
+                     const LimbMap &map, uint32_t polys, size_t poly_stride);
+// out = REDC(a * bm) [+ out] (bm in Montgomery form) for `polys` polynomials
+// of one stride, each times the same bm
 int launch_mul_mont(hck_context *ctx, uint64_t *out, const uint64_t *a, const uint64_t *bm,
-                    const LimbMap &map, int mode);
+                    const LimbMap &map, bool add = false, uint32_t polys = 1,
+                    size_t poly_stride = 0);
 // x -> x 2^64 mod q (into Montgomery form) or x 2^-64 (out of it), in place
 int launch_to_mont(hck_context *ctx, uint64_t *buf, const LimbMap &map, bool to);
 // tensor of (a0, a1) and (b0, b1) into out0..out2; poly stride given in words
@@ -449,6 +470,10 @@ struct KsBatch {
   const uint64_t *add0[kMaxBatch];
   const uint64_t *add1[kMaxBatch];
   const uint64_t *add0_src[kMaxBatch] = {};
+  // further addends without an automorphism, read at the positions written
+  // (so they may be the output), or null
+  const uint64_t *sum0[kMaxBatch] = {};
+  const uint64_t *sum1[kMaxBatch] = {};
 };
 int keyswitch_batch(hck_context *ctx, const KsBatch &batch, uint32_t level);
 // keyswitch_batch in the given workspace (ws_ks_rows rows per batch slot;
@@ -502,10 +527,12 @@ int launch_lt_sums(hck_context *ctx, const LtSumArgs &a, uint32_t level);
 int apply_galois_multi(hck_context *ctx, const hck_ciphertext *const *a, const uint32_t *g,
                        uint32_t n, const hck_galois_keys *gks, hck_ciphertext *const *out);
 // the same with the switch keys given, one per ciphertext (they may differ in
-// owner: batches across tenants)
+// owner: batches across tenants); with sum, out[i] = sum[i] + phi(a[i]), where
+// sum[i] has a[i]'s level and scale and may be out[i]
 int apply_galois_keys(hck_context *ctx, const hck_ciphertext *const *a, const uint32_t *g,
                       const hck_switch_key *const *keys, uint32_t n,
-                      hck_ciphertext *const *out);
+                      hck_ciphertext *const *out,
+                      const hck_ciphertext *const *sum = nullptr);
 // relinearizations of n 3-part ciphertexts (one level), each with its own
 // key, key-switched together; outputs distinct, out[i] may alias a[i]
 int relinearize_keys(hck_context *ctx, const hck_ciphertext *const *a,

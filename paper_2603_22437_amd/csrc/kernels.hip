@@ -11,30 +11,69 @@ namespace {
 
 constexpr int kThreads = 256;
 
-__global__ __launch_bounds__(kThreads) void k_copy(uint64_t *__restrict__ dst,
-                                                   const uint64_t *__restrict__ src,
-                                                   size_t words) {
-  size_t i = (size_t)blockIdx.x * kThreads + threadIdx.x;
-  size_t stride = (size_t)gridDim.x * kThreads;
-  for (; i < words; i += stride) dst[i] = src[i];
+// words of one polynomial of `polys`, two a thread (blockIdx.y: polynomial)
+__global__ __launch_bounds__(kThreads) void k_copy(uint64_t *__restrict__ dst, size_t dps,
+                                                   const uint64_t *__restrict__ src, size_t sps,
+                                                   size_t pairs) {
+  const size_t stride = (size_t)gridDim.x * kThreads;
+  ulonglong2 *d = (ulonglong2 *)(dst + blockIdx.y * dps);
+  const ulonglong2 *s = (const ulonglong2 *)(src + blockIdx.y * sps);
+  for (size_t i = (size_t)blockIdx.x * kThreads + threadIdx.x; i < pairs; i += stride) d[i] = s[i];
 }
 
-__global__ __launch_bounds__(kThreads) void k_addsub(uint64_t *out, const uint64_t *a,
+// The element-wise kernels take two words a thread (16-byte accesses) of row
+// blockIdx.y, most of polynomial blockIdx.z: a launch a polynomial takes most
+// of its 4.7 us (13 limbs at N = 2^16) to start and end.
+struct Words {
+  uint64_t w[2];
+};
+__device__ __forceinline__ Words ld2(const uint64_t *p) {
+  const ulonglong2 v = *(const ulonglong2 *)p;
+  return Words{{v.x, v.y}};
+}
+__device__ __forceinline__ void st2(uint64_t *p, Words v) {
+  *(ulonglong2 *)p = make_ulonglong2(v.w[0], v.w[1]);
+}
+
+__global__ __launch_bounds__(kThreads / 2) void k_addsub(uint64_t *out, const uint64_t *a,
                                                      const uint64_t *b, LimbMap map,
                                                      const ModConst *__restrict__ mc, int n,
                                                      int op) {
-  const int i = blockIdx.x * kThreads + threadIdx.x;
-  const size_t off = (size_t)map.row[blockIdx.y] * n + i;
+  const size_t off =
+      (size_t)map.row[blockIdx.y] * n + 2 * (blockIdx.x * (kThreads / 2) + threadIdx.x);
   const uint64_t q = mc[map.mod[blockIdx.y]].q;
-  uint64_t x = a[off];
-  uint64_t r;
-  if (op == 0)
-    r = add_mod(x, b[off], q);
-  else if (op == 1)
-    r = sub_mod(x, b[off], q);
-  else
-    r = x == 0 ? 0 : q - x;
-  out[off] = r;
+  Words x = ld2(a + off);
+  const Words y = ld2(b + off);
+#pragma unroll
+  for (int k = 0; k < 2; k++)
+    x.w[k] = op == 0 ? add_mod(x.w[k], y.w[k], q) : sub_mod(x.w[k], y.w[k], q);
+  st2(out + off, x);
+}
+
+// out_0 = a_0 + pt (pt in Montgomery form), out_p = a_p for p > 0
+__global__ __launch_bounds__(kThreads) void k_add_plain(uint64_t *out, const uint64_t *a,
+                                                        const uint64_t *pt, size_t ps, LimbMap map,
+                                                        const ModConst *__restrict__ mc, int n) {
+  const size_t row = (size_t)map.row[blockIdx.y] * n + 2 * (blockIdx.x * kThreads + threadIdx.x);
+  const ModConst m = mc[map.mod[blockIdx.y]];
+  Words x = ld2(a + blockIdx.z * ps + row);
+  if (blockIdx.z == 0) {
+    const Words y = ld2(pt + row);
+#pragma unroll
+    for (int k = 0; k < 2; k++) {
+      u128 t;
+      t.lo = y.w[k];
+      t.hi = 0;
+      x.w[k] = add_mod(x.w[k], redc(t, m.q, m.qinv), m.q);
+    }
+  }
+  st2(out + blockIdx.z * ps + row, x);
+}
+
+// row r of out = w[r] in every word: the evaluation form of a constant
+__global__ __launch_bounds__(kThreads) void k_fill_rows(uint64_t *out, RowScale v, int n) {
+  const uint64_t w = v.w[blockIdx.y];
+  st2(out + (size_t)blockIdx.y * n + 2 * (blockIdx.x * kThreads + threadIdx.x), Words{{w, w}});
 }
 
 // out = sum of n inputs mod q, row by row (rows of `map`)
@@ -99,20 +138,25 @@ __global__ __launch_bounds__(kThreads) void k_mulmod_rate(uint64_t *out, uint64_
   out[tid] = s;
 }
 
-// out = [+-] REDC(a * bm) [+ out]: mode 0 set, 1 add to out, 2 subtract from
-// out, 3 set negated (bm in Montgomery form, so REDC gives a * b mod q)
+// out = REDC(a * bm) [+ out] (bm in Montgomery form, so REDC gives a * b mod
+// q; one bm for every polynomial)
 __global__ __launch_bounds__(kThreads) void k_mul_mont(uint64_t *out, const uint64_t *a,
-                                                       const uint64_t *bm, LimbMap map,
+                                                       const uint64_t *bm, size_t ps, LimbMap map,
                                                        const ModConst *__restrict__ mc, int n,
-                                                       int mode) {
-  const int i = blockIdx.x * kThreads + threadIdx.x;
-  const size_t off = (size_t)map.row[blockIdx.y] * n + i;
+                                                       int add) {
+  const size_t row = (size_t)map.row[blockIdx.y] * n + 2 * (blockIdx.x * kThreads + threadIdx.x);
+  const size_t off = blockIdx.z * ps + row;
   const ModConst m = mc[map.mod[blockIdx.y]];
-  uint64_t r = redc(mul_wide(a[off], bm[off]), m.q, m.qinv);
-  if (mode == 1) r = add_mod(out[off], r, m.q);
-  else if (mode == 2) r = sub_mod(out[off], r, m.q);
-  else if (mode == 3) r = r == 0 ? 0 : m.q - r;
-  out[off] = r;
+  Words x = ld2(a + off);
+  const Words y = ld2(bm + row);
+#pragma unroll
+  for (int k = 0; k < 2; k++) x.w[k] = redc(mul_wide(x.w[k], y.w[k]), m.q, m.qinv);
+  if (add) {
+    const Words o = ld2(out + off);
+#pragma unroll
+    for (int k = 0; k < 2; k++) x.w[k] = add_mod(x.w[k], o.w[k], m.q);
+  }
+  st2(out + off, x);
 }
 
 __global__ __launch_bounds__(kThreads) void k_to_mont(uint64_t *buf, LimbMap map,
@@ -220,24 +264,57 @@ dim3 grid_rows(const hck_context *ctx, uint32_t rows, uint32_t z = 1) {
   return dim3(ctx->n / kThreads, rows, z);
 }
 
+// two words a thread
+dim3 grid_pairs(const hck_context *ctx, uint32_t rows, uint32_t polys) {
+  return dim3(ctx->n / (2 * kThreads), rows, polys);
+}
+
 }  // namespace
 
-int launch_copy(hck_context *ctx, uint64_t *dst, const uint64_t *src, size_t words) {
-  if (words == 0 || dst == src) return HCK_OK;
-  unsigned blocks = (unsigned)std::min<size_t>((words + kThreads - 1) / kThreads, 8192);
-  timing_begin(ctx, "copy", dim3(blocks), 16.0 * words);
-  k_copy<<<blocks, kThreads, 0, ctx->stream>>>(dst, src, words);
+int launch_copy_polys(hck_context *ctx, uint64_t *dst, size_t dps, const uint64_t *src, size_t sps,
+                      size_t words, uint32_t polys) {
+  if (words == 0 || polys == 0 || dst == src) return HCK_OK;
+  const size_t pairs = words / 2;  // words are whole limbs
+  const unsigned blocks = (unsigned)std::min<size_t>((pairs + kThreads - 1) / kThreads, 4096);
+  timing_begin(ctx, "copy", dim3(blocks, polys), 16.0 * words * polys);
+  k_copy<<<dim3(blocks, polys), kThreads, 0, ctx->stream>>>(dst, dps, src, sps, pairs);
   timing_end(ctx);
   HCK_HIP(ctx, hipGetLastError());
   return HCK_OK;
 }
 
+int launch_copy(hck_context *ctx, uint64_t *dst, const uint64_t *src, size_t words) {
+  return launch_copy_polys(ctx, dst, 0, src, 0, words, 1);
+}
+
 int launch_addsub(hck_context *ctx, uint64_t *out, const uint64_t *a, const uint64_t *b,
                   const LimbMap &map, int op) {
   if (map.n == 0) return HCK_OK;
-  timing_begin(ctx, "addsub", grid_rows(ctx, map.n), 24.0 * ctx->n * map.n);
-  k_addsub<<<grid_rows(ctx, map.n), kThreads, 0, ctx->stream>>>(out, a, b, map, ctx->d_mod,
-                                                                 ctx->n, op);
+  const dim3 grid = grid_rows(ctx, map.n);
+  timing_begin(ctx, "addsub", grid, 24.0 * ctx->n * map.n);
+  k_addsub<<<grid, kThreads / 2, 0, ctx->stream>>>(out, a, b, map, ctx->d_mod, ctx->n, op);
+  timing_end(ctx);
+  HCK_HIP(ctx, hipGetLastError());
+  return HCK_OK;
+}
+
+int launch_add_plain(hck_context *ctx, uint64_t *out, const uint64_t *a, const uint64_t *pt,
+                     const LimbMap &map, uint32_t polys, size_t poly_stride) {
+  const dim3 grid = grid_pairs(ctx, map.n, polys);
+  timing_begin(ctx, "add_plain", grid, (16.0 * polys + 8.0) * ctx->n * map.n);
+  k_add_plain<<<grid, kThreads, 0, ctx->stream>>>(out, a, pt, poly_stride, map, ctx->d_mod,
+                                                  ctx->n);
+  timing_end(ctx);
+  HCK_HIP(ctx, hipGetLastError());
+  return HCK_OK;
+}
+
+int launch_fill_rows(hck_context *ctx, uint64_t *out, uint32_t rows, const RowScale &v) {
+  if (rows == 0) return HCK_OK;
+  if (rows > (uint32_t)kMaxLimbs) return set_error(HCK_EINVAL, "too many rows");
+  const dim3 grid = grid_pairs(ctx, rows, 1);
+  timing_begin(ctx, "fill", grid, 8.0 * ctx->n * rows);
+  k_fill_rows<<<grid, kThreads, 0, ctx->stream>>>(out, v, ctx->n);
   timing_end(ctx);
   HCK_HIP(ctx, hipGetLastError());
   return HCK_OK;
@@ -320,12 +397,13 @@ int measure_mulmod_rate(hck_context *ctx, double *tera_per_s) {
 }
 
 int launch_mul_mont(hck_context *ctx, uint64_t *out, const uint64_t *a, const uint64_t *bm,
-                    const LimbMap &map, int mode) {
+                    const LimbMap &map, bool add, uint32_t polys, size_t poly_stride) {
   if (map.n == 0) return HCK_OK;
-  timing_begin(ctx, "mul_plain", grid_rows(ctx, map.n),
-               ((mode == 1 || mode == 2) ? 32.0 : 24.0) * ctx->n * map.n, (double)ctx->n * map.n);
-  k_mul_mont<<<grid_rows(ctx, map.n), kThreads, 0, ctx->stream>>>(out, a, bm, map, ctx->d_mod,
-                                                                   ctx->n, mode);
+  const dim3 grid = grid_pairs(ctx, map.n, polys);
+  timing_begin(ctx, "mul_plain", grid, ((add ? 24.0 : 16.0) * polys + 8.0) * ctx->n * map.n,
+               (double)ctx->n * map.n * polys);
+  k_mul_mont<<<grid, kThreads, 0, ctx->stream>>>(out, a, bm, poly_stride, map, ctx->d_mod, ctx->n,
+                                                 add ? 1 : 0);
   timing_end(ctx);
   HCK_HIP(ctx, hipGetLastError());
   return HCK_OK;

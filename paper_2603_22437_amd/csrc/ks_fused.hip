@@ -587,13 +587,15 @@ __attribute__((amdgpu_waves_per_eu(4))) void k_ks_contig_inner(
       for (int v = 0; v < P; v++) x[v] = ar.settle(x[v]);
       G::to_interleaved(lds, x, c, r);
       const uint64_t *add = p == 0 ? kb.add0[b] : kb.add1[b];
+      const uint64_t *sum = p == 0 ? kb.sum0[b] : kb.sum1[b];
       uint64_t *out = (p == 0 ? kb.out0[b] : kb.out1[b]) + (size_t)t * G::N;
 #pragma unroll
       for (int i = 0; i < P; i++) {
         const size_t pos = G::gaddr(g, G::ipoint(r, i));
         E v = ar.mul(ar.sub(a[i], x[i]), f);
         if (add) v += ar.load(add[(size_t)t * G::N + galois_src((uint32_t)pos, galois, LOGN)]);
-        out[pos] = ar.template canon<3072>(v);
+        if (sum) v += ar.load(sum[(size_t)t * G::N + pos]);
+        out[pos] = ar.template canon<4096>(v);
       }
     };
     // special limbs: ModDown's inverse contiguous pass, while the limb's
@@ -938,7 +940,8 @@ void launch_contig_inner(hck_context *ctx, const KsBatch &kb, const KsGeom &kg, 
     bool seen = false;
     for (uint32_t k = 0; k < b; k++) seen = seen || kb.key[k] == kb.key[b];
     keys += seen ? 0 : 1;
-    if (TAIL) adds += (kb.add0[b] ? nq : 0) + (kb.add1[b] ? nq : 0);
+    if (TAIL)
+      for (const uint64_t *a : {kb.add0[b], kb.add1[b], kb.sum0[b], kb.sum1[b]}) adds += a ? nq : 0;
   }
   const double ext = nb * (digits * limbs - q_limbs);  // transformed digit limbs
   // accumulators written, or (tail) conv read and outputs written

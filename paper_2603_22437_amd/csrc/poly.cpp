@@ -74,10 +74,9 @@ int hck_poly_eval(hck_context *ctx, const hck_ciphertext *x, const double *coeff
     const uint32_t a = 1u << (ceil_log2(k) - 1);  // largest power of two below k
     const hck_ciphertext *u = pw[a], *v = pw[k - a];
     const uint32_t lv = u->level < v->level ? u->level : v->level;
-    hck_ciphertext *ud = sc.get(), *vd = sc.get(), *t = sc.get();
-    TRY(hck_drop_level(ctx, u, lv, ud));
-    TRY(hck_drop_level(ctx, v, lv, vd));
-    TRY(hck_mul(ctx, ud, vd, t));
+    hck_ciphertext *t = sc.get();
+    const hck_ciphertext ud = at_level(u, lv), vd = at_level(v, lv);
+    TRY(hck_mul(ctx, &ud, &vd, t));
     pw[k] = sc.get();
     TRY(hck_relinearize(ctx, t, rlk, pw[k]));
     TRY(hck_rescale(ctx, pw[k], pw[k]));
@@ -86,12 +85,12 @@ int hck_poly_eval(hck_context *ctx, const hck_ciphertext *x, const double *coeff
   bool first = true;
   for (uint32_t k = 1; k <= degree; k++) {
     if (coeffs[k] == 0.0) continue;
-    hck_ciphertext *t = sc.get(), *term = first ? out : sc.get();
-    TRY(hck_drop_level(ctx, pw[k], lf + 1, t));
+    hck_ciphertext *term = first ? out : sc.get();
+    const hck_ciphertext t = at_level(pw[k], lf + 1);
     Pt pt;
-    TRY(hck_encode_const(ctx, coeffs[k], x->scale * (double)ctx->mods[lf + 1] / t->scale, lf + 1,
+    TRY(hck_encode_const(ctx, coeffs[k], x->scale * (double)ctx->mods[lf + 1] / t.scale, lf + 1,
                          &pt.p));
-    TRY(hck_mul_plain(ctx, t, pt.p, term));
+    TRY(hck_mul_plain(ctx, &t, pt.p, term));
     TRY(hck_rescale(ctx, term, term));
     if (!first) TRY(hck_add(ctx, out, term, out));
     first = false;

@@ -47,11 +47,11 @@ int ntt_pass(hck_context *ctx, uint64_t *buf, const LimbMap &map, bool inverse, 
   HCK_BY_RING(NttRing, ntt_pass(ctx, buf, map, inverse, strided, sc))
 }
 
-int rescale_fused(hck_context *ctx, uint64_t *out, const uint64_t *in, const uint64_t *last,
-                  uint64_t *tmp, uint32_t level, uint32_t polys) {
+int rescale_fused(hck_context *ctx, uint64_t *out, const uint64_t *in, uint64_t *tmp,
+                  uint32_t level, uint32_t polys) {
   if (level == 0 || polys == 0) return HCK_OK;
   if (level > (uint32_t)kMaxLimbs) return set_error(HCK_EINVAL, "too many limbs");
-  HCK_BY_RING(NttRing, rescale(ctx, out, in, last, tmp, level, polys))
+  HCK_BY_RING(NttRing, rescale(ctx, out, in, tmp, level, polys))
 }
 
 // Batches grow where each slot is small (low levels), so that a launch still

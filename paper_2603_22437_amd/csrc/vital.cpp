@@ -135,11 +135,12 @@ std::vector<uint32_t> owners(size_t members, uint32_t per) {
   return w;
 }
 
-// dst[i] = Rot(src[i], step), every member with its window's key, key-switched
-// together
+// dst[i] = Rot(src[i], step) (+ sum[i]), every member with its window's key,
+// key-switched together
 int rotate_members(hck_context *ctx, const std::vector<hck_ciphertext *> &src,
                    const std::vector<uint32_t> &win, int32_t step, const WindowKeys &wk,
-                   const std::vector<hck_ciphertext *> &dst) {
+                   const std::vector<hck_ciphertext *> &dst,
+                   const hck_ciphertext *const *sum = nullptr) {
   const uint32_t g = galois_of_step(ctx, step);
   std::vector<uint32_t> gs(src.size(), g);
   std::vector<const hck_switch_key *> keys(src.size());
@@ -150,20 +151,15 @@ int rotate_members(hck_context *ctx, const std::vector<hck_ciphertext *> &src,
     keys[i] = it->second;
   }
   return apply_galois_keys(ctx, src.data(), gs.data(), keys.data(), (uint32_t)src.size(),
-                           dst.data());
+                           dst.data(), sum);
 }
 
 // c_i <- c_i + Rot(c_i, step) + ... over `count` (a power of two) shifts, for
 // every member at once
 int rotsum(hck_context *ctx, const std::vector<hck_ciphertext *> &cs,
-           const std::vector<uint32_t> &win, int32_t step, uint32_t count, const WindowKeys &wk,
-           Scratch &sc) {
-  std::vector<hck_ciphertext *> tmp;
-  for (size_t i = 0; i < cs.size(); i++) tmp.push_back(sc.get());
-  for (uint64_t s = (uint64_t)step; s < (uint64_t)step * count; s *= 2) {
-    TRY(rotate_members(ctx, cs, win, (int32_t)s, wk, tmp));
-    for (size_t i = 0; i < cs.size(); i++) TRY(hck_add(ctx, cs[i], tmp[i], cs[i]));
-  }
+           const std::vector<uint32_t> &win, int32_t step, uint32_t count, const WindowKeys &wk) {
+  for (uint64_t s = (uint64_t)step; s < (uint64_t)step * count; s *= 2)
+    TRY(rotate_members(ctx, cs, win, (int32_t)s, wk, cs, cs.data()));
   return HCK_OK;
 }
 
@@ -284,9 +280,9 @@ static int front_units(hck_context *ctx, const hck_vital_plan *p,
   if (pe == 3 || pe == 5) {  // times p (dropped to the power's level)
     std::vector<hck_ciphertext *> tm, mo = fresh(U);
     for (uint32_t u = 0; u < U; u++) {
-      hck_ciphertext *pl = sc.get(), *tp = sc.get();
-      TRY(hck_drop_level(ctx, pw[u], m[u]->level, pl));
-      TRY(hck_mul(ctx, m[u], pl, tp));
+      hck_ciphertext *tp = sc.get();
+      const hck_ciphertext pl = at_level(pw[u], m[u]->level);
+      TRY(hck_mul(ctx, m[u], &pl, tp));
       tm.push_back(tp);
     }
     TRY(relin_rs(ctx, tm, uw, wk, mo));
@@ -297,15 +293,14 @@ static int front_units(hck_context *ctx, const hck_vital_plan *p,
   iq = fresh(2 * U);
   ts.clear();
   for (uint32_t u = 0; u < U; u++) {
-    hck_ciphertext *re2 = sc.get(), *im2 = sc.get(), *ti = sc.get(), *tq = sc.get();
-    TRY(hck_drop_level(ctx, re[u], m[u]->level, re2));
-    TRY(hck_drop_level(ctx, im[u], m[u]->level, im2));
-    TRY(hck_mul(ctx, m[u], re2, ti));
-    TRY(hck_mul(ctx, m[u], im2, tq));
+    hck_ciphertext *ti = sc.get(), *tq = sc.get();
+    const hck_ciphertext re2 = at_level(re[u], m[u]->level), im2 = at_level(im[u], m[u]->level);
+    TRY(hck_mul(ctx, m[u], &re2, ti));
+    TRY(hck_mul(ctx, m[u], &im2, tq));
     ts.insert(ts.end(), {ti, tq});
   }
   TRY(relin_rs(ctx, ts, uw2, wk, iq));
-  return rotsum(ctx, iq, uw2, 1, p->bins, wk, sc);
+  return rotsum(ctx, iq, uw2, 1, p->bins, wk);
 }
 
 // Levels of the frame tree over the list cur = (I_0, Q_0, I_1, Q_1, ...) of
@@ -314,18 +309,16 @@ static int front_units(hck_context *ctx, const hck_vital_plan *p,
 static int frame_tree(hck_context *ctx, std::vector<hck_ciphertext *> &cur, int32_t shift,
                       const WindowKeys &wk, Scratch &sc) {
   for (; cur.size() > 2; shift *= 2) {
-    std::vector<hck_ciphertext *> src, nxt;
-    for (size_t i = 2; i + 1 < cur.size(); i += 4) src.insert(src.end(), {cur[i], cur[i + 1]});
-    std::vector<hck_ciphertext *> rot(src.size());
-    for (auto &c : rot) c = sc.get();
-    TRY(rotate_members(ctx, src, std::vector<uint32_t>(src.size(), 0), -shift, wk, rot));
+    std::vector<hck_ciphertext *> src, left, nxt;
     for (size_t i = 0; i < cur.size(); i += 4) {
       if (i + 2 < cur.size()) {
-        TRY(hck_add(ctx, cur[i], rot[i / 2], cur[i]));
-        TRY(hck_add(ctx, cur[i + 1], rot[i / 2 + 1], cur[i + 1]));
+        left.insert(left.end(), {cur[i], cur[i + 1]});
+        src.insert(src.end(), {cur[i + 2], cur[i + 3]});
       }
       nxt.insert(nxt.end(), {cur[i], cur[i + 1]});
     }
+    TRY(rotate_members(ctx, src, std::vector<uint32_t>(src.size(), 0), -shift, wk, left,
+                       left.data()));
     cur = nxt;
   }
   return HCK_OK;
@@ -409,7 +402,7 @@ static int vital_eval_windows(hck_context *ctx, const hck_vital_plan *p,
       it[k] = iq[2 * k];
       qt[k] = iq[2 * k + 1];
     }
-    TRY(rotsum(ctx, e, one, r, t2, wk, sc));
+    TRY(rotsum(ctx, e, one, r, t2, wk));
   } else {
     // entries of the frame tree that holds every frame's I and Q at slot t R
     std::vector<hck_ciphertext *> tree;
@@ -449,7 +442,7 @@ static int vital_eval_windows(hck_context *ctx, const hck_vital_plan *p,
       TRY(mulpt_rs(ctx, w[k], p->bin_mask, O(k, 1)));
       bins.insert(bins.end(), {O(k, 0), O(k, 1)});
     }
-    TRY(rotsum(ctx, bins, two, 1, (uint32_t)r, wk, sc));
+    TRY(rotsum(ctx, bins, two, 1, (uint32_t)r, wk));
   }
   for (uint32_t k = 0; k < n; k++) {
     TRY(tap(k, 3, it[k]));
@@ -541,9 +534,7 @@ static int vital_eval_windows(hck_context *ctx, const hck_vital_plan *p,
         win.push_back(k);
       }
     }
-    std::vector<hck_ciphertext *> tmp = fresh((uint32_t)src.size());
-    TRY(rotate_members(ctx, src, win, -(int32_t)s, wk, tmp));
-    for (size_t i = 0; i < src.size(); i++) TRY(hck_add(ctx, src[i], tmp[i], src[i]));
+    TRY(rotate_members(ctx, src, win, -(int32_t)s, wk, src, src.data()));
   }
   std::vector<hck_ciphertext *> xs = fresh(2 * n);
   for (uint32_t k = 0; k < n; k++) {
@@ -555,7 +546,7 @@ static int vital_eval_windows(hck_context *ctx, const hck_vital_plan *p,
     TRY(mulpt_rs(ctx, dphi[2 * k + 1], p->dft_im_hr, hr_im));
     TRY(hck_add(ctx, xs[2 * k + 1], hr_im, xs[2 * k + 1]));
   }
-  TRY(rotsum(ctx, xs, two, r, t2, wk, sc));
+  TRY(rotsum(ctx, xs, two, r, t2, wk));
   for (uint32_t k = 0; k < n; k++) {
     TRY(tap(k, 11, xs[2 * k]));
     TRY(tap(k, 12, xs[2 * k + 1]));
@@ -581,7 +572,7 @@ static int vital_eval_windows(hck_context *ctx, const hck_vital_plan *p,
     TRY(mulpt_rs(ctx, sh[k], p->mask, O(k, 3)));
     chain.insert(chain.end(), {O(k, 2), O(k, 3)});
   }
-  return rotsum(ctx, chain, two, 1, lanes.group, wk, sc);
+  return rotsum(ctx, chain, two, 1, lanes.group, wk);
 }
 
 namespace hck {
