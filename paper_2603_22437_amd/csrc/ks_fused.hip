@@ -162,7 +162,7 @@ __device__ __forceinline__ void bconv_halves(uint64_t (&x)[NT][G::P],
                                              uint32_t na, int g, int r,
                                              const ModConst (&m)[NT]) {
   constexpr int P = G::P;
-  constexpr int CH = P < 4 ? P : 4, GS = NT == 1 ? 2 : 4;
+  constexpr int CH = (P < 8 ? P : 8) / NT;
   constexpr uint32_t kLow30 = (1u << 30) - 1;
 #pragma unroll
   for (int c0 = 0; c0 < P; c0 += CH) {
@@ -171,23 +171,20 @@ __device__ __forceinline__ void bconv_halves(uint64_t (&x)[NT][G::P],
     for (int t = 0; t < NT; t++)
 #pragma unroll
       for (int k = 0; k < CH; k++) lo[t][k] = m1[t][k] = m2[t][k] = hi[t][k] = 0;
-    uint64_t vv[GS][CH];
-    auto load = [&](uint32_t a0) {  // GS limbs' words in flight together
+    uint64_t v[CH], nx[CH];
 #pragma unroll
-      for (int s = 0; s < GS; s++) {
-        const size_t n = (size_t)min(a0 + s, na - 1) * G::N;
+    for (int k = 0; k < CH; k++) nx[k] = src[G::gaddr(g, G::ipoint(r, c0 + k))];
+    auto next = [&](uint32_t a) {  // takes limb a's words and loads limb a + 1's
+      const size_t n = (size_t)(a + 1 < na ? a + 1 : a) * G::N;
 #pragma unroll
-        for (int k = 0; k < CH; k++) vv[s][k] = src[n + G::gaddr(g, G::ipoint(r, c0 + k))];
+      for (int k = 0; k < CH; k++) {
+        v[k] = nx[k];
+        nx[k] = src[n + G::gaddr(g, G::ipoint(r, c0 + k))];
       }
     };
     if (na <= 8) {
-      for (uint32_t a0 = 0; a0 < na; a0 += GS) {
-        load(a0);
-#pragma unroll
-        for (int s = 0; s < GS; s++) {
-        const uint32_t a = a0 + s;
-        if (a >= na) break;
-        const auto &v = vv[s];
+      for (uint32_t a = 0; a < na; a++) {
+        next(a);
 #pragma unroll
         for (int t = 0; t < NT; t++) {
           const uint64_t c = cv[t][(size_t)a * cstride].w;
@@ -200,20 +197,14 @@ __device__ __forceinline__ void bconv_halves(uint64_t (&x)[NT][G::P],
             m1[t][k] += (uint64_t)(v0 + v1) * cs;
           }
         }
-        }
       }
 #pragma unroll
       for (int t = 0; t < NT; t++)
 #pragma unroll
         for (int k = 0; k < CH; k++) m1[t][k] -= lo[t][k] + hi[t][k];
     } else {
-      for (uint32_t a0 = 0; a0 < na; a0 += GS) {
-        load(a0);
-#pragma unroll
-        for (int s = 0; s < GS; s++) {
-        const uint32_t a = a0 + s;
-        if (a >= na) break;
-        const auto &v = vv[s];
+      for (uint32_t a = 0; a < na; a++) {
+        next(a);
 #pragma unroll
         for (int t = 0; t < NT; t++) {
           const uint64_t c = cv[t][(size_t)a * cstride].w;
@@ -226,7 +217,6 @@ __device__ __forceinline__ void bconv_halves(uint64_t (&x)[NT][G::P],
             m2[t][k] += (uint64_t)v1 * cl;
             hi[t][k] += (uint64_t)v1 * ch;
           }
-        }
         }
       }
     }
@@ -266,7 +256,7 @@ __device__ __forceinline__ void bconv_float(double (&x)[NT][G::P],
                                             uint32_t na, const ModConst *__restrict__ ms, int g,
                                             int r, const ModConst (&m)[NT]) {
   constexpr int P = G::P;
-  constexpr int CH = P < 4 ? P : 4, GS = NT == 1 ? 2 : 4;
+  constexpr int CH = (P < 8 ? P : 8) / NT;
   constexpr uint64_t kExp = 0x4330000000000000ull;          // 2^52 + (low bits)
   constexpr double kOff = 4503599627370496.0 + 16777216.0;  // 2^52 + 2^24
 #pragma unroll
@@ -276,21 +266,16 @@ __device__ __forceinline__ void bconv_float(double (&x)[NT][G::P],
     for (int t = 0; t < NT; t++)
 #pragma unroll
       for (int k = 0; k < CH; k++) lo[t][k] = mi[t][k] = hi[t][k] = 0.0;
-    for (uint32_t a0 = 0; a0 < na; a0 += GS) {
-      // GS limbs' words in flight together (past the last limb: the last again,
-      // unused)
-      uint64_t vv[GS][CH];
+    uint64_t v[CH], nx[CH];
 #pragma unroll
-      for (int s = 0; s < GS; s++) {
-        const size_t n = (size_t)min(a0 + s, na - 1) * G::N;
+    for (int k = 0; k < CH; k++) nx[k] = src[G::gaddr(g, G::ipoint(r, c0 + k))];
+    for (uint32_t a = 0; a < na; a++) {
+      const size_t n = (size_t)(a + 1 < na ? a + 1 : a) * G::N;
 #pragma unroll
-        for (int k = 0; k < CH; k++) vv[s][k] = src[n + G::gaddr(g, G::ipoint(r, c0 + k))];
+      for (int k = 0; k < CH; k++) {
+        v[k] = nx[k];
+        nx[k] = src[n + G::gaddr(g, G::ipoint(r, c0 + k))];
       }
-#pragma unroll
-      for (int s = 0; s < GS; s++) {
-      const uint32_t a = a0 + s;
-      if (a >= na) break;
-      const auto &v = vv[s];
       const bool wide = ms[a].qd == 0.0;  // uniform
 #pragma unroll
       for (int k = 0; k < CH; k++) {
@@ -314,7 +299,6 @@ __device__ __forceinline__ void bconv_float(double (&x)[NT][G::P],
             mi[t][k] = __builtin_fma(v2, c.es, mi[t][k]);
           }
         }
-      }
       }
     }
 #pragma unroll
@@ -375,14 +359,14 @@ __device__ __forceinline__ void with_ks_arith(const ModConst &m, F &&f) {
 // source in flight per register: 224 us against 254 us for 8 slots of 72 rows)
 // and for conversions on whole words.
 template <int LOGN, bool PAIR, bool S30>
-using ConvPass = typename PassPick<!S30 ? 2 : pass_kind(split_a(LOGN), true),
+using ConvPass = typename PassPick<PAIR || !S30 ? 2 : pass_kind(split_a(LOGN), true),
                                    split_a(LOGN), LOGN, true>::type;
 
 // K3: workgroup y converts the targets of group y (one, or two of one
 // arithmetic) of slot z.  Two targets share the reads of the sources.
 template <int LOGN, bool PAIR, bool S30>
 __global__ __launch_bounds__((ConvPass<LOGN, PAIR, S30>::THREADS))
-__attribute__((amdgpu_waves_per_eu(!S30 ? 3 : PAIR ? 4 : 6))) void k_modup_strided(
+__attribute__((amdgpu_waves_per_eu(!PAIR && S30 ? 4 : 3))) void k_modup_strided(
     uint64_t *__restrict__ ws, const ConvGroup *__restrict__ groups,
     const ConvC *__restrict__ conv, KsGeom kg, const ModConst *__restrict__ mc,
     const Tw *__restrict__ tw) {
@@ -655,7 +639,7 @@ __attribute__((amdgpu_waves_per_eu(4))) void k_ks_contig_inner(
 // special limbs.
 template <int LOGN, bool PAIR, bool S30>
 __global__ __launch_bounds__((ConvPass<LOGN, PAIR, S30>::THREADS))
-__attribute__((amdgpu_waves_per_eu(!S30 ? 3 : PAIR ? 4 : 6))) void k_moddown_strided(
+__attribute__((amdgpu_waves_per_eu(!PAIR && S30 ? 4 : 3))) void k_moddown_strided(
     uint64_t *__restrict__ ws, const ConvC *__restrict__ down_conv,
     const uint64_t *__restrict__ hneg, const ConvGroup *__restrict__ groups, KsGeom kg,
     const ModConst *__restrict__ mc, const Tw *__restrict__ tw) {
@@ -881,7 +865,7 @@ int ks_modup(hck_context *ctx, const KsBatch &kb, const KsGeom &kg, uint64_t *ws
     launch(paired ? k_modup_strided<LOGN, true, false> : k_modup_strided<LOGN, false, false>,
            kNttThreads);
   else if (paired)
-    launch(k_modup_strided<LOGN, true, true>, ConvPass<LOGN, true, true>::THREADS);
+    launch(k_modup_strided<LOGN, true, true>, kNttThreads);
   else
     launch(k_modup_strided<LOGN, false, true>, ConvPass<LOGN, false, true>::THREADS);
   timing_end(ctx);
@@ -931,7 +915,7 @@ int ks_down_conv(hck_context *ctx, uint32_t nb, const KsGeom &kg, uint64_t *ws, 
     launch(paired ? k_moddown_strided<LOGN, true, false> : k_moddown_strided<LOGN, false, false>,
            kNttThreads);
   else if (paired)
-    launch(k_moddown_strided<LOGN, true, true>, ConvPass<LOGN, true, true>::THREADS);
+    launch(k_moddown_strided<LOGN, true, true>, kNttThreads);
   else
     launch(k_moddown_strided<LOGN, false, true>, ConvPass<LOGN, false, true>::THREADS);
   timing_end(ctx);
