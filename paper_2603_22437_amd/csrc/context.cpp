@@ -122,47 +122,78 @@ int make_split(hck_context *ctx, const std::vector<Powers> &pws, int log_a,
   return HCK_OK;
 }
 
+// f and g with f 2^50 + g = e modulo t, both of about sqrt(t): the point
+// nearest to (0, e) in the lattice of (f, g) with f 2^50 + g = 0 mod t, over
+// its Gauss-reduced basis.  (All values stay below 2^51, products below 2^102.)
+void short_pair(int64_t e, uint64_t t, int64_t *f, int64_t *g) {
+  using wide = __int128;
+  auto nearest = [](wide a, wide b) {
+    if (b < 0) a = -a, b = -b;
+    return a >= 0 ? (a + b / 2) / b : -((b / 2 - a) / b);
+  };
+  wide uf = 1, ug = -(wide)h_centred((1ull << 50) % t, t), wf = 0, wg = t;
+  for (;;) {
+    if (uf * uf + ug * ug > wf * wf + wg * wg) {
+      std::swap(uf, wf);
+      std::swap(ug, wg);
+    }
+    const wide m = nearest(uf * wf + ug * wg, uf * uf + ug * ug);
+    const wide nf = wf - m * uf, ng = wg - m * ug;
+    if (nf * nf + ng * ng >= wf * wf + wg * wg) break;  // each turn shortens w
+    wf = nf;
+    wg = ng;
+  }
+  const wide det = uf * wg - ug * wf;
+  const wide x = nearest(-(wide)e * wf, det), y = nearest(uf * e, det);
+  *f = (int64_t)-(x * uf + y * wf);
+  *g = (int64_t)(e - (x * ug + y * wg));
+}
+
 // The constants of one conversion's sources src[0..na) (moduli) to modulus t,
 // hat(a) = the constant of source a, in rows out[a * stride] and the centring
 // row out[na * stride].  Returns whether the conversion in doubles keeps every
-// column exact (bconv_float): with |v0|, |v1| <= 2^24 + 2^19 (a source in the
-// floating-point range is below 2^50 + 2^44) and v2 < 2^11,
-//   sum |c0 + c1| (2^25 + 2^20) + sum |es| 2^11 <= 2^53,
-//   sum (|c0| + |c1|) (2^24 + 2^19) + sum (|e0| + |es|) 2^11 <= 2^52.
+// sum exact (bconv_float): over each 8 sources, with |v| <= 2^49 + 2^44 (a
+// source in the floating-point range is below 2^50 + 2^44), v2 < 2^10 and what
+// each product rounds off within 2^49,
+//   sum |c| (2^49 + 2^44) + |f| 2^10 + 2^49 < 2^101,
+//   sum 2^49 + |g| 2^10 < 2^53
+// (with a margin for the rounding of these sums themselves).
 template <class Hat>
 bool conv_constants(const std::vector<uint64_t> &src, uint64_t t, Hat &&hat, ConvC *out,
                     size_t stride) {
-  auto halves = [](int64_t c, double *lo, double *hi) {
-    const int64_t h = (c + (1 << 24)) >> 25;
-    *lo = (double)(c - h * (1 << 25));
-    *hi = (double)h;
-  };
-  const uint64_t r64 = h_r64(t), off = ((1ull << 49) + (1ull << 24)) % t;
+  const uint64_t r64 = h_r64(t), off = (1ull << 49) % t;
+  const double u49 = 562949953421312.0, u50 = 2 * u49;
   uint64_t k = 0;
-  double cross = 0, mid = 0;
+  bool ok = true;
+  double sum = 0, err = 0;
   for (size_t a = 0; a < src.size(); a++) {
     const uint64_t c = hat(a);
     ConvC &o = out[a * stride];
     o.w = h_mulmod(c, r64, t);
-    o.c0 = o.c1 = o.cs = o.e0 = o.es = 0;
+    o.c = o.f = o.g = 0;
     if (!h_float_modulus(t)) continue;
-    halves(h_centred(c, t), &o.c0, &o.c1);
-    o.cs = o.c0 + o.c1;
+    if (a % 8 == 0) {  // later blocks start from the value of those before
+      sum = 0;
+      err = a ? 2 * u50 : 0;
+    }
+    o.c = (double)h_centred(c, t);
     k = (uint64_t)(((unsigned __int128)off * c + k) % t);
-    double e1 = 0;
     if (!h_float_modulus(src[a])) {
-      halves(h_centred(h_mulmod(c, (1ull << 50) % t, t), t), &o.e0, &e1);
-      o.es = o.e0 + e1;
+      int64_t f, g;
+      short_pair(h_centred(h_mulmod(c, (1ull << 50) % t, t), t), t, &f, &g);
+      o.f = (double)f * u50;
+      o.g = (double)g;
     }
     const auto abs = [](double d) { return d < 0 ? -d : d; };
-    cross += abs(o.cs) * ((1 << 25) + (1 << 20)) + abs(o.es) * 2048;
-    mid += (abs(o.c0) + abs(o.c1)) * ((1 << 24) + (1 << 19)) + (abs(o.e0) + abs(o.es)) * 2048;
+    sum += abs(o.c) * (u49 + 17592186044416.0) + abs(o.f) * 1024 + u49;
+    err += u49 + abs(o.g) * 1024;
+    ok = ok && sum < 0.999999 * 0x1p101 && err < 0.999999 * 0x1p53;
   }
   ConvC &o = out[src.size() * stride];
   o.w = 0;
-  o.c1 = o.cs = o.e0 = o.es = 0;
-  o.c0 = h_float_modulus(t) ? (double)h_centred(k, t) : 0;
-  return cross <= 9007199254740992.0 && mid <= 4503599627370496.0;
+  o.f = o.g = 0;
+  o.c = h_float_modulus(t) ? (double)h_centred(k, t) : 0;
+  return ok;
 }
 
 }  // namespace

@@ -36,15 +36,15 @@ struct ModConst {
   double qd, qid;
 };
 
-// One constant c of a basis conversion, from source limb a to a target
-// modulus (ks_fused.hip): in Montgomery form for integer targets; for targets
-// on doubles its centred value in 25-bit halves c = c1 2^25 + c0, cs = c0 + c1,
-// and, where the source's prime is not in the floating-point range, the halves
-// of c 2^50 mod t (e0 and es = e0 + e1).  The row after the last source holds
-// in c0 the constant that undoes the centring of the sources.
+// One constant of a basis conversion, from source limb a to a target modulus
+// (ks_fused.hip): in Montgomery form (w) for integer targets; for targets on
+// doubles its centred value c and, where the source's prime is not in the
+// floating-point range, f (a multiple of 2^50) and g with c 2^50 = f + g modulo
+// the target.  The row after the last source holds in c the constant that
+// undoes the centring of the sources.
 struct alignas(16) ConvC {
   uint64_t w;
-  double c0, c1, cs, e0, es;
+  double c, f, g;
 };
 
 // Targets that one workgroup of a basis conversion converts together: ext rows (from

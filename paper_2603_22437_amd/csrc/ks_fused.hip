@@ -238,17 +238,21 @@ __device__ __forceinline__ void bconv_halves(uint64_t (&x)[NT][G::P],
   }
 }
 
-// The sums for targets on doubles, within 1/2 q.  A source word is centred
-// and split, v = v1 2^25 + v0 + (2^49 + 2^24) with |v0|, |v1| about 2^24; the
-// constant is centred and split likewise, and
-//   sum v c = L + 2^25 M + 2^50 H + K,
-//   L = sum v0 c0, H = sum v1 c1, M = sum (v0 + v1)(c0 + c1) - L - H,
-// three FP64 multiply-adds a product, every column an exact integer (the
-// bounds, over this context's constants, are checked when it is made:
-// hck_context::conv_f).  K undoes the centring.  A source whose prime is not
-// in the floating-point range has its bits from 50 on as
-// one more small factor with the constant c 2^50 mod t.  The columns are
-// combined by Horner's rule modulo q, where products by 2^25 are exact.
+// The sums for targets on doubles, within 1/2 q.  A source word less 2^49 is a
+// double v, |v| <= 2^49 + 2^44, and the constant a centred double c.  The sum
+// runs in T, which starts at 1.5 2^102 and stays in that binade, so that each
+// multiply-add rounds to a multiple of 2^50, and the part rounded off is exact
+// in a second multiply-add:
+//   T' = T + v c (rounded),  E += v c - (T' - T),  |v c - (T' - T)| <= 2^49,
+// four operations a product and no splitting of the source word.  (Splitting
+// both factors into 25-bit halves took three multiply-adds a product and about
+// seven operations a source: one rotation at N = 2^16 166.5 us against 163.6,
+// 21 at level 3 559.6 against 550.6, on one card in turn.)  A source whose prime is not in the floating-point
+// range has its bits from 50 on as one more factor v2 < 2^10 with the constant
+// c 2^50 = f 2^50 + g mod t, f and g short: v2 f 2^50 is exact in T, v2 g in E.
+// T and E are reduced every 8 sources; the host has checked that they stay
+// exact over this context's constants (hck_context::conv_f).  The row after the
+// last source undoes the 2^49.
 template <class G, int NT>
 __device__ __forceinline__ void bconv_float(double (&x)[NT][G::P],
                                             const uint64_t *__restrict__ src,
@@ -257,15 +261,25 @@ __device__ __forceinline__ void bconv_float(double (&x)[NT][G::P],
                                             int r, const ModConst (&m)[NT]) {
   constexpr int P = G::P;
   constexpr int CH = (P < 8 ? P : 8) / NT;
-  constexpr uint64_t kExp = 0x4330000000000000ull;          // 2^52 + (low bits)
-  constexpr double kOff = 4503599627370496.0 + 16777216.0;  // 2^52 + 2^24
+  constexpr uint64_t kExp = 0x4330000000000000ull;               // 2^52 + (low bits)
+  constexpr double kOff = 4503599627370496.0 + 562949953421312.0;  // 2^52 + 2^49
+  constexpr double kBase = 0x1.8p102;
 #pragma unroll
   for (int c0 = 0; c0 < P; c0 += CH) {
-    double lo[NT][CH], mi[NT][CH], hi[NT][CH];
+    double sum[NT][CH], err[NT][CH];
 #pragma unroll
     for (int t = 0; t < NT; t++)
 #pragma unroll
-      for (int k = 0; k < CH; k++) lo[t][k] = mi[t][k] = hi[t][k] = 0.0;
+      for (int k = 0; k < CH; k++) {
+        sum[t][k] = kBase;
+        err[t][k] = 0.0;
+      }
+    // what the columns stand for, an integer below 2^51: a reduction leaves
+    // 2^-52 of its argument and q / 2
+    auto value = [&](int t, int k) {
+      const ArF ar{m[t].qd, m[t].qid};
+      return ar.reduce(sum[t][k] - kBase) + ar.reduce(err[t][k]);
+    };
     uint64_t v[CH], nx[CH];
 #pragma unroll
     for (int k = 0; k < CH; k++) nx[k] = src[G::gaddr(g, G::ipoint(r, c0 + k))];
@@ -276,27 +290,34 @@ __device__ __forceinline__ void bconv_float(double (&x)[NT][G::P],
         v[k] = nx[k];
         nx[k] = src[n + G::gaddr(g, G::ipoint(r, c0 + k))];
       }
+      if (a == 8) {
+#pragma unroll
+        for (int t = 0; t < NT; t++)
+#pragma unroll
+          for (int k = 0; k < CH; k++) {
+            err[t][k] = value(t, k);
+            sum[t][k] = kBase;
+          }
+      }
       const bool wide = ms[a].qd == 0.0;  // uniform
+      const uint64_t mask = wide ? (1ull << 50) - 1 : ~0ull;
 #pragma unroll
       for (int k = 0; k < CH; k++) {
-        const double v0 = __longlong_as_double((long long)((v[k] & 0x1ffffff) | kExp)) - kOff;
-        const uint64_t top = wide ? (v[k] >> 25) & 0x1ffffff : v[k] >> 25;
-        const double v1 = __longlong_as_double((long long)(top | kExp)) - kOff;
-        const double vs = v0 + v1;
+        const double d = __longlong_as_double((long long)((v[k] & mask) | kExp)) - kOff;
 #pragma unroll
         for (int t = 0; t < NT; t++) {
-          const ConvC &c = cv[t][(size_t)a * cstride];
-          lo[t][k] = __builtin_fma(v0, c.c0, lo[t][k]);
-          hi[t][k] = __builtin_fma(v1, c.c1, hi[t][k]);
-          mi[t][k] = __builtin_fma(vs, c.cs, mi[t][k]);
+          const double c = cv[t][(size_t)a * cstride].c;
+          const double next = __builtin_fma(d, c, sum[t][k]);
+          err[t][k] += __builtin_fma(d, c, sum[t][k] - next);
+          sum[t][k] = next;
         }
         if (wide) {
           const double v2 = (double)(uint32_t)(v[k] >> 50);
 #pragma unroll
           for (int t = 0; t < NT; t++) {
             const ConvC &c = cv[t][(size_t)a * cstride];
-            lo[t][k] = __builtin_fma(v2, c.e0, lo[t][k]);
-            mi[t][k] = __builtin_fma(v2, c.es, mi[t][k]);
+            sum[t][k] = __builtin_fma(v2, c.f, sum[t][k]);
+            err[t][k] = __builtin_fma(v2, c.g, err[t][k]);
           }
         }
       }
@@ -304,14 +325,10 @@ __device__ __forceinline__ void bconv_float(double (&x)[NT][G::P],
 #pragma unroll
     for (int t = 0; t < NT; t++) {
       const ArF ar{m[t].qd, m[t].qid};
-      const double c25 = 33554432.0, q25 = 33554432.0 * m[t].qid;
-      const double kt = cv[t][(size_t)na * cstride].c0;
+      const double kt = cv[t][(size_t)na * cstride].c;
 #pragma unroll
       for (int k = 0; k < CH; k++) {
-        const double mid = mi[t][k] - lo[t][k] - hi[t][k];
-        const double u = __builtin_fma(-__builtin_rint(hi[t][k] * q25), ar.q, hi[t][k] * c25) + mid;
-        const double w = __builtin_fma(-__builtin_rint(u * q25), ar.q, u * c25) + (lo[t][k] + kt);
-        x[t][c0 + k] = ar.reduce(w);
+        x[t][c0 + k] = ar.reduce(value(t, k) + kt);
         asm volatile("" ::"v"(x[t][c0 + k]) : "memory");  // one chunk at a time
       }
     }
