@@ -527,7 +527,8 @@ int build_context(const hck_params *prm, int device, void *stream, hck_context *
   }
 
   // targets per workgroup of the basis conversions: single, and pairs of
-  // consecutive targets of one arithmetic
+  // consecutive targets of one arithmetic (the kernel picks the first target's
+  // for both; a modulus of 2^60 or more overflows in the class below it)
   std::vector<ConvGroup> groups;
   auto group_targets = [&](const std::vector<ConvGroup> &one, bool pairs) {
     const std::pair<uint32_t, uint32_t> none((uint32_t)groups.size(), 0);
@@ -535,8 +536,7 @@ int build_context(const hck_params *prm, int device, void *stream, hck_context *
     for (size_t i = 0; i < one.size(); i++) {
       ConvGroup g = one[i];
       if (pairs && i + 1 < one.size() && one[i + 1].digit == g.digit &&
-          h_float_modulus(ctx->mods[g.mod[0]]) ==
-              h_float_modulus(ctx->mods[one[i + 1].mod[0]])) {
+          h_arith_class(ctx->mods[g.mod[0]]) == h_arith_class(ctx->mods[one[i + 1].mod[0]])) {
         g.row[1] = one[i + 1].row[0];
         g.mod[1] = one[i + 1].mod[0];
         g.n = 2;

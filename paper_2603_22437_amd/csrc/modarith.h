@@ -155,6 +155,12 @@ inline bool h_float_modulus(uint64_t q) {
   return q >= (1ull << 26) && q < (1ull << 50) + (1ull << 44);
 }
 
+// The arithmetic a modulus runs in (with_arith in ntt_core.h): doubles,
+// integers below 2^60, integers from 2^60 on.
+inline int h_arith_class(uint64_t q) {
+  return h_float_modulus(q) ? 0 : q < (1ull << 60) ? 1 : 2;
+}
+
 inline uint64_t h_bits(double d) {
   uint64_t u;
   __builtin_memcpy(&u, &d, 8);

@@ -116,3 +116,31 @@ def test_rotations_in_place_match_copies(name, level, count):
             ctx.rotate_many(cts, step, gks, outs=cts)
         for c, w in zip(cts, want):
             np.testing.assert_array_equal(ctx.ciphertext_export(c)[0], w)
+
+
+@pytest.mark.parametrize("kind,level,count", [("specials", 10, 12), ("chain", 11, 16)])
+def test_pairs_across_2_60_match_oracle(kind, level, count):
+    """Launches large enough to convert two targets in a workgroup, where the
+    integer moduli of a pair lie on either side of 2^60: the last q and the
+    first special prime of the ModUp, and two of the q chain in the ModDown."""
+    log_n, two_n, taken = 15, 2 << 15, set()
+    low = _primes(two_n, 1 << 55, 12, taken, -1)
+    high = _primes(two_n, 1 << 61, 4, taken, -1)
+    if kind == "specials":   # digits 0 and 1 pair (q_10, p_0)
+        q, p, dnum = low, high, 3
+    else:                    # the ModUp's targets are special primes alone
+        q = [low[0], high[0], low[1], high[1]] + low[2:10]
+        p, dnum = _primes(two_n, 1 << 59, 4, taken, -1), 1
+    prm = dict(name=f"pairs/{kind}", log_n=log_n, n=1 << log_n, q=q, p=p, dnum=dnum,
+               scale=2.0 ** 40)
+    o, ctx = O.Oracle(prm), H.Context.from_params(prm)
+    sk, s_o = ctx.keygen_secret(1), o.keygen_secret(1)
+    step = 3
+    g = o.galois_element(step)
+    gks, gko = ctx.keygen_rotation(sk, [step], 5), {g: o.keygen_galois(s_o, g, 5)}
+    for values in ("uniform", "top"):
+        r = _residues(o.qmods(level), o.n, values, 70 + level)
+        want = o.rotate(O.Ciphertext(r, level, 2.0 ** 40), step, gko).polys
+        cts = [ctx.ciphertext_import(r, level, 2.0 ** 40) for _ in range(count)]
+        for y in ctx.rotate_many(cts, step, gks):
+            np.testing.assert_array_equal(ctx.ciphertext_export(y)[0], want, f"{kind}, {values}")
