@@ -335,9 +335,9 @@ __device__ __forceinline__ void bconv_float(double (&x)[NT][G::P],
   }
 }
 
-// The conversion in a target's arithmetic.  S30: every modulus is below 2^60
-// and the columns of this context's constants stay exact in doubles; other
-// contexts convert on whole words.
+// The conversion in a target's arithmetic, within converted_bound.  S30: every
+// modulus is below 2^60 and the columns of this context's constants stay exact
+// in doubles; other contexts convert on whole words.
 template <class G, int NT, bool S30, class Ar>
 __device__ __forceinline__ void bconv(typename Ar::E (&x)[NT][G::P],
                                       const uint64_t *__restrict__ src,
@@ -692,15 +692,14 @@ __attribute__((amdgpu_waves_per_eu(!PAIR && S30 ? 4 : 3))) void k_moddown_stride
         if constexpr (Ar::kFloat) at = Ar{ms[NT - 1].qd, ms[NT - 1].qid};
         else at = Ar{ms[NT - 1].q, ms[NT - 1].nq};
       }
-      // minus (P-1)/2: within q (doubles, both terms within 1/2), in [0, 2q)
-      // (integers)
+      // minus (P-1)/2, within 1/2 (doubles) or in [0, q) (integers)
       typename Ar::E h = at.load(hneg[mi[t]]);
       if constexpr (Ar::kFloat) h = at.reduce(h);
 #pragma unroll
       for (int i = 0; i < P; i++) x[t][i] += h;
       if (t == 0) __syncthreads();
-      G::template forward<Ar, Ar::kFloat ? 2 * Ar::kReduced : 2048>(
-          lds, x[t], c, r, tw + (size_t)mi[t] * kTwLen, lw[t], at);
+      G::template forward<Ar, moddown_bound<Ar, S30>()>(lds, x[t], c, r,
+                                                        tw + (size_t)mi[t] * kTwLen, lw[t], at);
       uint64_t *out = slot + ((size_t)kg.off_conv + p * kg.L + mi[t]) * G::N;
 #pragma unroll
       for (int v = 0; v < P; v++) out[G::gaddr(g, G::bpoint(r, v))] = Ar::bits(x[t][v]);

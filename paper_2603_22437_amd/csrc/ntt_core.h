@@ -706,6 +706,17 @@ using Pass = typename PassPick<pass_kind(LOGR, STRIDED), LOGR, LOGN, STRIDED>::t
 template <class Ar>
 constexpr int twisted_bound() { return Ar::product(Ar::kFloat ? 8065 : 0); }
 
+// What a basis conversion leaves: within 1/2 where it ran in doubles (S30 of
+// ks_fused.hip), fully reduced words where it ran on integers.
+template <class Ar, bool S30>
+constexpr int converted_bound() { return Ar::kFloat && S30 ? Ar::kReduced : Ar::kCanonical; }
+// The same plus ModDown's rounding term, which is within 1/2 (doubles) or a
+// fully reduced word (integers).
+template <class Ar, bool S30>
+constexpr int moddown_bound() {
+  return converted_bound<Ar, S30>() + (Ar::kFloat ? Ar::kReduced : Ar::kCanonical);
+}
+
 // Slot of the input that lands in slot j under X -> X^g (bit-reversed
 // evaluation order: slot j holds the value at psi^(2 brv(j) + 1)).
 __device__ __forceinline__ uint32_t galois_src(uint32_t j, uint32_t g, int log_n) {
