@@ -24,6 +24,8 @@
 //       pass of conv and out_i = (acc_i - conv_i) P^-1 (+ phi_g(addend)_i)
 // Switching the special limbs first keeps the Q limbs' accumulators out of
 // memory (2 (l + 1) rows a switch, written once and read once).
+// Small switches take K4 over all limbs at once, and K7 is the tail alone
+// (kTogetherMaxLog).
 //
 // Workspace: batch slot b occupies rows [b R, (b+1) R) of ws_ks (R rows of N
 // words): y [L] | ext [dnum][L+K] | acc [2][L+K] | conv [2][L].  Rows between
@@ -57,6 +59,17 @@ constexpr size_t kPairMinBlocks = 3072;
 // a CU.  One special basis of 8 limbs at N = 2^16 (512 tiles) 22.6 -> 18.9 us;
 // 24 limbs (1536 tiles) 45.9 -> 49.1 us, so larger launches do not.
 constexpr size_t kSplitMaxBlocks = 512;
+// Largest ring at which a switch of at most kSplitMaxBlocks tiles, over all its
+// extended limbs, takes every key product in one launch and its accumulators
+// through memory.  All its tiles run at once, so its time is the chain of its
+// launches, and the Q limbs' products beside the special limbs' take one pass
+// a digit off that chain; larger switches are bound by what they move.  One
+// switch in its turn, special limbs first / all at once: N = 2^11, one limb and
+// one special prime 51.4 / 46.3 us; N = 2^12, 12 limbs and 4 66.7 / 56.6 us;
+// N = 2^15, 12 and 4 (512 tiles) 75.4 / 73.4 us, two of them (1024 tiles)
+// 92.8 / 93.3 us, four 130 / 140 us; N = 2^17, 2 limbs and 2 (512 tiles)
+// 79.0 / 79.6 us.
+constexpr int kTogetherMaxLog = 15;
 
 template <int LOGN>
 __global__ __launch_bounds__(kNttThreads) void k_ks_intt_gather(
@@ -707,9 +720,11 @@ __attribute__((amdgpu_waves_per_eu(!PAIR && S30 ? 4 : 3))) void k_moddown_stride
   });
 }
 
-// K7 where the accumulators come from memory (hoisted rotations and shared
-// ModDowns): per Q limb, the forward contiguous pass of conv and the tail.
-template <int LOGN>
+// K7 where the accumulators come from memory (small switches, hoisted
+// rotations and shared ModDowns): per Q limb, the forward contiguous pass of
+// conv and the tail.  SUM: some slots have further addends (the test for them
+// by itself cost 13 hoisted rotations of 13 limbs at N = 2^16 0.4-1 %).
+template <int LOGN, bool SUM>
 __global__ __launch_bounds__(kNttThreads) void k_moddown_contig_tail(
     uint64_t *__restrict__ ws, KsBatch kb, const Tw *__restrict__ pinv, KsGeom kg,
     const ModConst *__restrict__ mc, const Tw *__restrict__ tw, const Tw *__restrict__ tt) {
@@ -726,6 +741,7 @@ __global__ __launch_bounds__(kNttThreads) void k_moddown_contig_tail(
   const uint64_t *cin = slot + ((size_t)kg.off_conv + p * kg.L + li) * G::N;
   const uint64_t *u = slot + ((size_t)kg.off_acc + p * kg.ne + li) * G::N;
   const uint64_t *add = p == 0 ? kb.add0[b] : kb.add1[b];
+  const uint64_t *sum = !SUM ? nullptr : p == 0 ? kb.sum0[b] : kb.sum1[b];
   const uint32_t galois = kb.galois[b];
   uint64_t *out = (p == 0 ? kb.out0[b] : kb.out1[b]) + (size_t)li * G::N;
   with_arith(mc[li], [&](auto ar) {
@@ -746,7 +762,8 @@ __global__ __launch_bounds__(kNttThreads) void k_moddown_contig_tail(
       const size_t pos = G::gaddr(g, G::ipoint(r, i));
       E v = ar.mul(ar.sub(ar.load(u[pos]), x[i]), f);
       if (add) v += ar.load(add[(size_t)li * G::N + galois_src((uint32_t)pos, galois, LOGN)]);
-      out[pos] = ar.template canon<3072>(v);
+      if (sum) v += ar.load(sum[(size_t)li * G::N + pos]);
+      out[pos] = ar.template canon<SUM ? 4096 : 3072>(v);
     }
   });
 }
@@ -1002,11 +1019,19 @@ int ks_moddown(hck_context *ctx, const KsBatch &kb, const KsGeom &kg, uint64_t *
   }
   if ((rc = ks_down_conv<LOGN>(ctx, nb, kg, ws, special_contig_done))) return rc;
   double adds = 0;
-  for (uint32_t b = 0; b < nb; b++) adds += (kb.add0[b] ? nq : 0) + (kb.add1[b] ? nq : 0);
+  bool sums = false;
+  for (uint32_t b = 0; b < nb; b++) {
+    sums = sums || kb.sum0[b] || kb.sum1[b];
+    for (const uint64_t *a : {kb.add0[b], kb.add1[b], kb.sum0[b], kb.sum1[b]}) adds += a ? nq : 0;
+  }
   timing_begin(ctx, "ks_moddown_tail", dim3(GB::BLOCKS, nb, 2 * nq),
                8.0 * N * (3.0 * 2 * nq * nb + adds), N * (0.5 * B + 1) * 2 * nq * nb);
-  k_moddown_contig_tail<LOGN><<<dim3(GB::BLOCKS, nb, 2 * nq), kNttThreads, 0, ctx->stream>>>(
-      ws, kb, ctx->d_pinv, kg, ctx->d_mod, ctx->d_tw, ctx->split[0].twist);
+  auto launch = [&](auto kernel) {
+    kernel<<<dim3(GB::BLOCKS, nb, 2 * nq), kNttThreads, 0, ctx->stream>>>(
+        ws, kb, ctx->d_pinv, kg, ctx->d_mod, ctx->d_tw, ctx->split[0].twist);
+  };
+  constexpr bool kSums = LOGN <= kTogetherMaxLog;  // no other caller has any
+  launch(kSums && sums ? k_moddown_contig_tail<LOGN, kSums> : k_moddown_contig_tail<LOGN, false>);
   timing_end(ctx);
   HCK_HIP(ctx, hipGetLastError());
   return HCK_OK;
@@ -1017,6 +1042,11 @@ int ks_run(hck_context *ctx, const KsBatch &kb, uint32_t level, uint64_t *ws) {
   const KsGeom kg = make_geom(ctx, level);
   int rc;
   if ((rc = ks_modup<LOGN>(ctx, kb, kg, ws))) return rc;
+  using GB = Pass<split_b(LOGN), LOGN, false>;
+  if (LOGN <= kTogetherMaxLog && (size_t)GB::BLOCKS * kb.n * kg.ne <= kSplitMaxBlocks) {
+    launch_contig_inner<LOGN, false>(ctx, kb, kg, ws, 0, kg.ne, true);
+    return ks_moddown<LOGN>(ctx, kb, kg, ws, true);
+  }
   launch_contig_inner<LOGN, false>(ctx, kb, kg, ws, 0, kg.K, false);
   if ((rc = ks_down_conv<LOGN>(ctx, kb.n, kg, ws, false))) return rc;
   launch_contig_inner<LOGN, true>(ctx, kb, kg, ws, kg.K, kg.nq, false);

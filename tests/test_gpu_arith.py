@@ -144,3 +144,47 @@ def test_pairs_across_2_60_match_oracle(kind, level, count):
         cts = [ctx.ciphertext_import(r, level, 2.0 ** 40) for _ in range(count)]
         for y in ctx.rotate_many(cts, step, gks):
             np.testing.assert_array_equal(ctx.ciphertext_export(y)[0], want, f"{kind}, {values}")
+
+
+@pytest.mark.parametrize("name,level,count,together",
+                         [("edge11", 0, 1, True), ("edge11", 2, 7, True), ("gest12", 11, 1, True),
+                          ("gest12", 11, 16, True), ("mid14", 7, 2, True), ("mid14", 7, 3, False),
+                          ("mix15", 11, 1, True), ("mix15", 11, 2, False),
+                          ("edge17", 0, 1, False)])
+def test_small_switches_match_oracle(name, level, count, together):
+    """Switches whose tiles all run at once take their key products in one
+    launch and the tail by itself; on either side of that line rotations (into
+    other ciphertexts and in place) and relinearizations are bit-exact."""
+    if name == "mid14":
+        taken = set()
+        q = _primes(2 << 14, 1 << 60, 1, taken, -1) + _primes(2 << 14, 1 << 50, 7, taken, -1)
+        prm = dict(name=name, log_n=14, n=1 << 14, q=q, dnum=3, scale=2.0 ** 40,
+                   p=_primes(2 << 14, 1 << 60, 3, taken, -1))
+    else:
+        prm = S.params(name)
+    o, ctx = O.Oracle(prm), H.Context.from_params(prm)
+    sk, s_o = ctx.keygen_secret(1), o.keygen_secret(1)
+    step = 5
+    g = o.galois_element(step)
+    gks, gko = ctx.keygen_rotation(sk, [step], 5), {g: o.keygen_galois(s_o, g, 5)}
+    rlk, rlk_o = ctx.keygen_relin(sk, 7), o.keygen_relin(s_o, 7)
+    rs = [S.uniform_residues(o.qmods(level), o.n, 90 + i, 2) for i in range(count)]
+    cts = [ctx.ciphertext_import(r, level, 2.0 ** 40) for r in rs]
+    cts_o = [O.Ciphertext(r, level, 2.0 ** 40) for r in rs]
+    same = lambda got, want, what: [
+        np.testing.assert_array_equal(ctx.ciphertext_export(x)[0], y.polys, what)
+        for x, y in zip(got, want)]
+    outs = [ctx.ciphertext() for _ in cts]
+    ctx.trace(True)
+    ctx.rotate_many(cts, step, gks, outs=outs)
+    names = [r[0] for r in ctx.trace_read()]
+    ctx.trace(False)
+    last = "ks_moddown_tail" if together else "ks_inner_tail"
+    assert names[-1] == last and names.count("ks_contig_inner") == 1, names
+    want = [o.rotate(c, step, gko) for c in cts_o]
+    same(outs, want, "rotate_many")
+    prods = [ctx.mul(c, c) for c in cts]
+    ctx.rotate_many(cts, step, gks, outs=cts)
+    same(cts, want, "in place")
+    ctx.relinearize_many(prods, rlk, outs=prods)
+    same(prods, [o.relinearize(o.tensor(c, c), rlk_o) for c in cts_o], "relinearize in place")
