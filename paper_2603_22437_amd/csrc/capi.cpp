@@ -260,8 +260,6 @@ int make_switch_key(hck_context *ctx, const hck_secret_key *sk, const uint64_t *
         m.row[i - lo] = (uint16_t)i;
         m.mod[i - lo] = (uint8_t)i;
         sc.w[i - lo] = pm;
-        sc.wp[i - lo] = 0;
-        sc.add[i - lo] = 0;
       }
       rc = launch_scalar_mac(ctx, b, sp_m, m, sc);
     }

@@ -448,7 +448,6 @@ int build_context(const hck_params *prm, int device, void *stream, hck_context *
     c.r64 = h_r64(q);
     c.r64_shoup = h_shoup(c.r64, q);
     c.ninv = h_invmod(n % q, q);
-    c.ninv_shoup = h_shoup(c.ninv, q);
     c.r2 = h_mulmod(c.r64, c.r64, q);
     c.one_shoup = h_shoup(1, q);
     c.nq = 0 - q;

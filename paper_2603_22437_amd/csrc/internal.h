@@ -28,7 +28,6 @@ struct ModConst {
   uint64_t r64;         // 2^64 mod q (into Montgomery form, Shoup constant)
   uint64_t r64_shoup;
   uint64_t ninv;        // N^-1 mod q
-  uint64_t ninv_shoup;
   uint64_t r2;          // 2^128 mod q (Montgomery fix-up of a plain product)
   uint64_t one_shoup;   // floor(2^64 / q): Shoup companion of 1 (reduction of any word)
   uint64_t nq;          // 2^64 - q
@@ -64,12 +63,9 @@ struct LimbMap {
   uint8_t mod[kMaxRows];
 };
 
-// Per-row Shoup multiplier and additive constant applied at the end of an
-// inverse NTT (x -> x w + a mod q); indexed like LimbMap rows (list index).
+// One word per row of a launch, by list index of a LimbMap or by row.
 struct RowScale {
   uint64_t w[kMaxLimbs];
-  uint64_t wp[kMaxLimbs];
-  uint64_t add[kMaxLimbs];
 };
 
 }  // namespace hck
