@@ -345,8 +345,8 @@ int relinearize_keys(hck_context *ctx, const hck_ciphertext *const *a,
       hck_ciphertext *y = out[s0 + b];
       scales[b] = x->scale;
       TRY(ensure_ct(ctx, y, 2));
-      // (d0, d1) + KeySwitch(d2): d2 is read before the final launch writes
-      // the outputs, and the addends are read at the positions written
+      // (d0, d1) + KeySwitch(d2): the final launch reads d2, which the outputs
+      // never overlap, and the addends at the positions it writes
       kb.key[b] = rlk[s0 + b]->data;
       kb.galois[b] = 1;
       kb.d[b] = x->data + 2 * ps;
@@ -929,7 +929,8 @@ static int addsub_ct(hck_context *ctx, const hck_ciphertext *a, const hck_cipher
   const double scale = a->scale;
   TRY(ensure_ct(ctx, out, size));
   const size_t ps = poly_stride(ctx);
-  // one launch a polynomial: the launch trace's form of this operation
+  // one launch a polynomial: the launch trace's records of an addition have
+  // that shape, and callers read them
   for (uint32_t p = 0; p < size; p++)
     TRY(launch_addsub(ctx, out->data + p * ps, a->data + p * ps, b->data + p * ps,
                       qmap(ctx, level), op));

@@ -100,8 +100,8 @@ struct hck_context {
   hck::ConvGroup *d_groups = nullptr;
   std::vector<std::pair<uint32_t, uint32_t>> groups[2];       // [pairs?][level]: (first, count)
   std::vector<std::pair<uint32_t, uint32_t>> down_groups[2];  // the same of the ModDown (row unused)
-  // targets on doubles are converted in doubles: every sum of products of
-  // halves stays exact for this context's constants
+  // targets on doubles are converted in doubles: the sums of bconv_float stay
+  // exact for this context's constants
   bool conv_f = false;
 
   // key-switch workspace (device)
@@ -120,8 +120,8 @@ struct hck_context {
   // splits one below and one above the default are built when first chosen
   // and kept until the context is destroyed (recorded graphs may read them)
   uint8_t ntt_a = 0;
-  // every modulus below 2^60: the basis conversions sum products of 30-bit
-  // halves in carry-free 64-bit columns
+  // every modulus below 2^60: the basis conversions to integer targets sum
+  // products of 30-bit halves in carry-free 64-bit columns
   bool bconv30 = false;
   // key switches per launch sequence at each level, chosen by the autotuner
   // (hck_autotune_keyswitch) or set by the caller; 0: the built-in rule
@@ -445,17 +445,17 @@ uint64_t *ws_rot(hck_context *ctx);   // [kMaxBatch][L][N]: copies of aliased in
 uint64_t *ws_tmp(hck_context *ctx);   // [3][L+K][N]: general temporary
 uint64_t *ws_pq(hck_context *ctx);    // [kLtOut][2][L+K][N]: extended-basis sums
 // Up to kMaxBatch key switches at one level in one sequence of launches,
-// slot b with its own switching key key[b] ([dnum][2][L+K][N], Montgomery
-// form; slots that share a key read it through the cache):
+// slot b with its own switching key key[b] ([dnum][2][L+K][N], in the key
+// switch's form, launch_key_form; slots that share a key read it through the
+// cache):
 // (out0[b], out1[b]) = KeySwitch(phi_g(d[b])) + (phi_g(add0[b]), phi_g(add1[b])).
 // d and the addends are [level+1][N] in evaluation form; g = 1 for no
 // automorphism; null addends are skipped.  out rows must not overlap d (but
-// see add0_src); with g != 1 they must not overlap the addends.  An output that aliases its
-// input's c0 sets add0_src[b] = c0 and add0[b] = a workspace copy of
-// [level+1][N] words: the first launch copies c0 there, and phi_g(d) into the
-// workspace, before the last launch, which reads both across workgroups,
-// overwrites them (null: add0 and d are read in place, and the outputs must
-// not overlap them).
+// see add0_src), which the last launch reads again; with g != 1 they must not
+// overlap the addends either.  An output that aliases its input's c0 sets
+// add0_src[b] = c0 and add0[b] = a workspace copy of [level+1][N] words: the
+// first launch copies c0 there, and phi_g(d) into the workspace, before the
+// last launch, which reads both across workgroups, overwrites them.
 struct KsBatch {
   uint32_t n;
   const uint64_t *key[kMaxBatch];
@@ -514,7 +514,6 @@ int keyswitch_hoisted(hck_context *ctx, const uint64_t *c0, const uint64_t *c1, 
 int keyswitch_core(hck_context *ctx, const uint64_t *d, uint32_t galois, uint32_t level,
                    const hck_switch_key *key, uint64_t *out0, uint64_t *out1, const uint64_t *add0,
                    const uint64_t *add1);
-// fused inner sums of the linear-transform evaluator over limbs 0..level
 // inner sums of the linear-transform evaluator over limbs 0..level
 int launch_lt_sums(hck_context *ctx, const LtSumArgs &a, uint32_t level);
 // automorphisms a[i] -> phi_{g[i]}(a[i]) of n ciphertexts (same level), each

@@ -569,7 +569,7 @@ __attribute__((amdgpu_waves_per_eu(4))) void k_ks_contig_inner(
           k1[i] = ktile[TILE + pos - tile0];
         }
         if constexpr (Ar::kFloat) {
-          // |x| <= q and a centred key: products within 0.7 q
+          // |x| <= q and a centred key: products within kProduct2
           a0[i] += ar.mul2(x[i], Ar::raw(k0[i]));
           a1[i] += ar.mul2(x[i], Ar::raw(k1[i]));
         } else {
@@ -578,7 +578,11 @@ __attribute__((amdgpu_waves_per_eu(4))) void k_ks_contig_inner(
         }
       }
       if constexpr (Ar::kFloat) {
-        // within 6.1 q at all times (each set's partial sums within 3.3 q)
+        // reduced after 8 products (a set's: after 4), so that the sum before a
+        // reduction, and what the tail takes conv from, stay in range
+        static_assert(ArF::fits(ArF::kReduced + 8 * ArF::kProduct2));
+        static_assert(ArF::fits(ArF::kReduced + 7 * ArF::kProduct2 + ArF::kReduced));
+        static_assert(ArF::fits(2 * (ArF::kReduced + 3 * ArF::kProduct2) + ArF::kReduced));
         if ((j & 7) >= (SPLIT ? 6 : 7)) {
 #pragma unroll
           for (int i = 0; i < P; i++) {
@@ -803,7 +807,7 @@ __global__ __launch_bounds__(256) void k_ks_inner_gather(uint64_t *__restrict__ 
     const ArF ar{m.qd, m.qid};
     double s0 = 0.0, s1 = 0.0;
     digits([&](uint32_t j, uint64_t x, uint64_t k0, uint64_t k1) {
-      const double xd = ar.load(x);  // products within 0.7 q, sums within 6.1 q
+      const double xd = ar.load(x);  // bounds as in k_ks_contig_inner
       s0 += ar.mul2(xd, ArF::raw(k0));
       s1 += ar.mul2(xd, ArF::raw(k1));
       if ((j & 7) == 7) {

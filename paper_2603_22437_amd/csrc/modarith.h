@@ -150,7 +150,8 @@ inline uint64_t h_inv64(uint64_t q) {
 }
 
 // Moduli whose residues the transforms keep in doubles (ntt_core.h): large
-// enough that a quotient by q stays exact, small enough that 8 q fits 53 bits.
+// enough that a quotient by q stays exact, small enough that 53 bits hold
+// 7.87 q, which the bounds of the passes (ArF::fits) stay within.
 inline bool h_float_modulus(uint64_t q) {
   return q >= (1ull << 26) && q < (1ull << 50) + (1ull << 44);
 }

@@ -3,8 +3,9 @@
 // callers that cannot allocate device memory (code under stream capture,
 // serving loops that forbid allocation).
 //
-// The array holds one key-switch batch slot (ws_ks_rows rows of N words) and
-// a copy of c0 for an output that aliases its input.  Every rotation on a GPU
+// The array holds one key-switch batch slot (ws_ks_rows rows of N words, a copy
+// of phi_g(c1) for an output that aliases its input among them) and a copy of
+// c0 for such an output.  Every rotation on a GPU
 // shares that GPU's array: calls that overlap in time on one GPU (two
 // streams, two contexts, two threads) race and must be serialized by the
 // caller.  Nothing in it has to start at zero: each key-switch stage writes
@@ -86,13 +87,13 @@ int rotate_noalloc(hck_context *ctx, const hck_ciphertext *a, int32_t step,
     uint64_t *ws = nullptr;
     int rc = scratch_address(ctx, &ws);
     if (rc) return rc;
-    // (phi_g(c0), 0) + KeySwitch(phi_g(c1)); the final launch gathers c0
-    // while it writes the output, so an output aliasing the input reads a
-    // copy of c0 placed after the key-switch slot
+    // (phi_g(c0), 0) + KeySwitch(phi_g(c1)); the final launch gathers both
+    // parts while it writes the output, so for an output aliasing the input it
+    // reads copies: of c0 after the key-switch slot, of phi_g(c1) inside it
     KsBatch kb;
     const uint64_t *c0 = a->data;
     if (out == a) {
-      kb.add0_src[0] = a->data;    // copied by the first launch
+      kb.add0_src[0] = a->data;    // the first launch makes the copies
       c0 = ws + ws_ks_rows(ctx) * n;
     }
     kb.n = 1;
