@@ -73,9 +73,9 @@ struct ArF {
   static constexpr int kReduced = 514;
   static constexpr int kCanonical = 1024;
   // |a b mod q| of mul2 for |a| <= q, |b| <= q/2: 1/2 plus the errors of c from
-  // rounding a b, 1/q and their product, each 2^-53 of q/2 <= 2^49 s (units
-  // of 2^-10: 64 s)
-  static constexpr int kProduct2 = 512 + 3 * scaled(64);
+  // rounding a b, 1/q and their product, each 2^-53 of q/2 <= 2^49 s (65 and
+  // less in units of q / 1024)
+  static constexpr int kProduct2 = 512 + 3 * 66;
   static constexpr int reduced(int) { return kReduced; }
   static constexpr int kTrivial = 1;  // leading stages whose products by 1 are left out
 
