@@ -162,10 +162,6 @@ int embed_small_host(hck_context *ctx, uint64_t *buf, const std::vector<int32_t>
   return rc;
 }
 
-bool scales_match(double a, double b) {
-  return std::fabs(a - b) <= std::ldexp(std::max(std::fabs(a), std::fabs(b)), -30);
-}
-
 // residues (host, coefficient domain) -> evaluation form rows of buf, checked < q
 int import_rows(hck_context *ctx, uint64_t *buf, const uint64_t *res, uint32_t polys,
                 uint32_t rows_per_poly, uint32_t nlimbs) {

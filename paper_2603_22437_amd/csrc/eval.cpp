@@ -76,6 +76,11 @@ int apply_galois_keys(hck_context *ctx, const hck_ciphertext *const *a, const ui
   for (uint32_t i = 0; i < n; i++) {
     if (a[i]->size != 2) return set_error(HCK_EINVAL, "rotation needs a 2-part ciphertext");
     if (a[i]->level != level) return set_error(HCK_ELEVEL, "batched rotations need one level");
+    if (sum) {
+      if (sum[i]->size != 2) return set_error(HCK_EINVAL, "rotate-and-add needs 2-part ciphertexts");
+      if (sum[i]->level != level) return set_error(HCK_ELEVEL, "levels differ");
+      if (!scales_match(sum[i]->scale, a[i]->scale)) return set_error(HCK_ESCALE, "scales differ");
+    }
     for (uint32_t k = 0; k < n; k++) {
       if (k < i && out[k] == out[i]) return set_error(HCK_EINVAL, "batched outputs must be distinct");
       if (k != i && out[k] == a[i])
@@ -93,7 +98,7 @@ int apply_galois_keys(hck_context *ctx, const hck_ciphertext *const *a, const ui
     for (uint32_t b = 0; b < kb.n; b++) {
       const hck_ciphertext *x = a[s + b];
       hck_ciphertext *y = out[s + b];
-      scales[b] = x->scale;
+      scales[b] = sum ? sum[s + b]->scale : x->scale;
       // (phi_g(c0), 0) + KeySwitch(phi_g(c1)).  Both parts are gathered through
       // phi_g by the final launch while it writes the outputs: an output that
       // aliases this input gets copies to read instead

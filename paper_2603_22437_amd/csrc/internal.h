@@ -2,6 +2,8 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+#include <cmath>
 #include <cstddef>
 #include <cstdint>
 #include <map>
@@ -214,6 +216,11 @@ struct hck_ciphertext {
 };
 
 namespace hck {
+// whether two ciphertexts' scales agree as far as an addition asks
+inline bool scales_match(double a, double b) {
+  return std::fabs(a - b) <= std::ldexp(std::max(std::fabs(a), std::fabs(b)), -30);
+}
+
 // The first level + 1 limbs of a ciphertext, as an input of the calls that
 // follow: a view of its buffer (limbs are stored first to last at a fixed
 // stride), never an output and never kept.
@@ -522,8 +529,8 @@ int launch_lt_sums(hck_context *ctx, const LtSumArgs &a, uint32_t level);
 int apply_galois_multi(hck_context *ctx, const hck_ciphertext *const *a, const uint32_t *g,
                        uint32_t n, const hck_galois_keys *gks, hck_ciphertext *const *out);
 // the same with the switch keys given, one per ciphertext (they may differ in
-// owner: batches across tenants); with sum, out[i] = sum[i] + phi(a[i]), where
-// sum[i] has a[i]'s level and scale and may be out[i]
+// owner: batches across tenants); with sum, out[i] = sum[i] + phi(a[i]) with
+// the checks and the scale (sum[i]'s) of an addition; sum[i] may be out[i]
 int apply_galois_keys(hck_context *ctx, const hck_ciphertext *const *a, const uint32_t *g,
                       const hck_switch_key *const *keys, uint32_t n,
                       hck_ciphertext *const *out,

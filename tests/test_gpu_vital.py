@@ -331,3 +331,46 @@ def test_vital_per_frame_packing_decodes_at_benchmark_ring():
         dec = ctx.decode(ctx.decrypt(sk, g)).real
         for slot, v in want[name].items():
             assert abs(dec[slot] - v) < decoded_tol(v), (name, slot, dec[slot], v)
+
+
+def _small_window(seed):
+    """gest12 context, plan, keys and the encrypted frames of one window."""
+    prm = S.params("gest12")
+    ctx = H.Context.from_params(prm)
+    sk = ctx.keygen_secret(1)
+    cfg = S.vital_pipeline_config(frames=32, bins=32, fps=4.0)
+    l0 = len(prm["q"]) - 1
+    plan = HV.encode_plan(ctx, cfg, l0)
+    steps = sorted(set(ctx.vital_required_steps(plan)) | set(ctx.vital_frames_required_steps(plan)))
+    gks, rlk = ctx.keygen_rotation(sk, steps, 5), ctx.keygen_relin(sk, 7)
+    z = S.vital_window(seed, cfg["frames"], cfg["bins"], fps=cfg["fps"])
+    return prm, ctx, sk, cfg, plan, gks, rlk, z, l0
+
+
+def test_vital_frames_scales():
+    """Frames whose scales differ: the sums of the frame tree refuse scales
+    that an addition refuses, and keep their left addend's scale."""
+    prm, ctx, sk, cfg, plan, gks, rlk, z, l0 = _small_window(1005)
+    polys = []
+    for t in range(cfg["frames"]):
+        for v in (z[t].real, z[t].imag):
+            x = np.zeros(ctx.n_slots)
+            x[: cfg["bins"]] = v
+            polys.append(ctx.ciphertext_export(
+                ctx.encrypt_sk(sk, ctx.encode(x, prm["scale"], l0), 700 + len(polys)))[0])
+
+    def run(delta):   # every frame but the first at scale (1 + delta)
+        cts = [ctx.ciphertext_import(p, l0, prm["scale"] * (1 + (delta if i > 1 else 0)))
+               for i, p in enumerate(polys)]
+        return [ctx.ciphertext_export(y)
+                for y in ctx.vital_eval_frames(plan, cts[::2], cts[1::2], gks, rlk)]
+
+    want = run(0.0)
+    # energies go with the square of the scale, I and Q with its fifth power:
+    # 0.3 and 0.75 of the tolerance 2^-30, then 0.6 and 1.5 of it
+    for (r, lvl, sc), (r0, lvl0, sc0) in zip(run(0.15 * 2.0 ** -30), want):
+        assert (lvl, sc) == (lvl0, sc0)
+        assert np.array_equal(r, r0)
+    with pytest.raises(H.HckError) as e:
+        run(0.3 * 2.0 ** -30)
+    assert "scales differ" in str(e.value)
