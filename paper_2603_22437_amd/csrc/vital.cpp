@@ -5,6 +5,7 @@
 // batched key switch, so one window issues as few key-switch
 // launch sequences as its dependency depth allows.
 #include <algorithm>
+#include <set>
 #include <vector>
 
 #include "internal.h"
@@ -158,8 +159,17 @@ int rotate_members(hck_context *ctx, const std::vector<hck_ciphertext *> &src,
 // every member at once
 int rotsum(hck_context *ctx, const std::vector<hck_ciphertext *> &cs,
            const std::vector<uint32_t> &win, int32_t step, uint32_t count, const WindowKeys &wk) {
-  for (uint64_t s = (uint64_t)step; s < (uint64_t)step * count; s *= 2)
-    TRY(rotate_members(ctx, cs, win, (int32_t)s, wk, cs, cs.data()));
+  // a caller's ciphertext may stand for several outputs: rotations into
+  // others then, and one addition after the other
+  const bool apart = std::set<hck_ciphertext *>(cs.begin(), cs.end()).size() == cs.size();
+  Scratch sc(ctx);
+  std::vector<hck_ciphertext *> tmp;
+  for (size_t i = 0; !apart && i < cs.size(); i++) tmp.push_back(sc.get());
+  for (uint64_t s = (uint64_t)step; s < (uint64_t)step * count; s *= 2) {
+    TRY(rotate_members(ctx, cs, win, (int32_t)s, wk, apart ? cs : tmp,
+                       apart ? cs.data() : nullptr));
+    for (size_t i = 0; i < tmp.size(); i++) TRY(hck_add(ctx, cs[i], tmp[i], cs[i]));
+  }
   return HCK_OK;
 }
 

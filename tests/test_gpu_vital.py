@@ -374,3 +374,37 @@ def test_vital_frames_scales():
     with pytest.raises(H.HckError) as e:
         run(0.3 * 2.0 ** -30)
     assert "scales differ" in str(e.value)
+
+
+def test_vital_outputs_may_repeat():
+    """One ciphertext given for two outputs of a sum: the call is accepted, the
+    other outputs are what they are with four ciphertexts, and the repeated one
+    takes both outputs' sums one after the other."""
+    prm, ctx, sk, cfg, plan, gks, rlk, z, l0 = _small_window(1006)
+    v = np.zeros(ctx.n_slots, dtype=np.complex128)
+    v[: z.size] = z.reshape(-1)
+    re = ctx.encrypt_sk(sk, ctx.encode(v.real, prm["scale"], l0), 100)
+    im = ctx.encrypt_sk(sk, ctx.encode(v.imag, prm["scale"], l0), 101)
+    want, taps = ctx.vital_eval_taps(plan, re, im, gks, rlk)
+    export = ctx.ciphertext_export
+
+    def both(x, step, count):
+        for _ in range(count.bit_length() - 1):
+            t = ctx.rotate(x, step, gks)
+            x = ctx.add(ctx.add(x, t), t)
+            step *= 2
+        return x
+
+    for first, tap, operand, count in (
+            (0, 2, "bin_mask", cfg["bins"]),
+            (2, 14, "mask", HV.lane_group(cfg))):
+        outs = [ctx.ciphertext() for _ in range(4)]
+        outs[first + 1] = outs[first]
+        ctx.vital_eval(plan, re, im, gks, rlk, outputs=outs)
+        for i in {0, 1, 2, 3} - {first, first + 1}:
+            assert np.array_equal(export(outs[i])[0], export(want[i])[0]), i
+        x = ctx.rescale(ctx.mul_plain(taps[tap], plan._keep[operand]))
+        r, lvl, sc = export(outs[first])
+        r0, lvl0, sc0 = export(both(x, 1, count))
+        assert (lvl, sc) == (lvl0, sc0)
+        assert np.array_equal(r, r0), first
