@@ -40,6 +40,14 @@ HBM_PEAK_GBS = 8000.0                       # MI355X HBM3E, GB/s
 VALU_LANE_RATE = 256 * 64 * 2.4e9           # full-rate VALU lane operations / s
 MAD_PER_MULMOD = 10                         # v_mad_u64_u32 per 61-bit Shoup product
 MULMOD_PEAK = VALU_LANE_RATE / MAD_PER_MULMOD
+FP64_PER_MULMOD = 6                         # FP64 operations per product on doubles
+FP64_MULMOD_PEAK = VALU_LANE_RATE / FP64_PER_MULMOD
+
+
+def on_doubles(q: int) -> bool:
+    """Whether the library's transforms run modulus q on doubles."""
+    return 1 << 26 <= q < (1 << 50) + (1 << 44)
+
 
 FRAMES, BINS, N1 = 200, 64, 20
 
@@ -288,10 +296,13 @@ def main():
     avg_ms = dom["ms"] / dom["launches"]
     gbs = dom["bytes"] / dom["launches"] / (avg_ms * 1e-3) / 1e9
     mms = dom["mulmods"] / dom["launches"] / (avg_ms * 1e-3)
-    hbm_frac, alu_frac = gbs / HBM_PEAK_GBS, mms / MULMOD_PEAK
+    # the transforms' products run on doubles for most moduli, the inner sums'
+    # on integers
+    alu_peak = MULMOD_PEAK if dom_name == "lt_inner" else FP64_MULMOD_PEAK
+    hbm_frac, alu_frac = gbs / HBM_PEAK_GBS, mms / alu_peak
     if alu_frac > hbm_frac:
         roof = {"bound": "alu", "achieved": round(mms / 1e12, 4),
-                "peak": round(MULMOD_PEAK / 1e12, 4), "unit": "Tmulmod/s",
+                "peak": round(alu_peak / 1e12, 4), "unit": "Tmulmod/s",
                 "frac": round(alu_frac, 4)}
     else:
         roof = {"bound": "hbm", "achieved": round(gbs, 1), "peak": HBM_PEAK_GBS,
@@ -383,8 +394,8 @@ def main():
         "roofline": roof,
         # key switching (the hot path's dominant cost) as a whole: full
         # rotations with distinct keys (R3) against both ceilings of one
-        # rotation (151 MB at 8 TB/s; 165 M modular products at the measured
-        # product rate)
+        # rotation (151 MB at 8 TB/s; 165 M modular products at the rates of
+        # rotation_ceilings)
         "roofline_keyswitch": {
             "rotations_per_s": rotation_modes["R3_16ct_16_keys_rot_per_s"],
             "hbm_ceiling_rot_per_s": ceilings["hbm_ceiling_rot_per_s"],
@@ -401,6 +412,7 @@ def main():
 
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "hbm_traffic_vital_window.md")
 KERNEL_SOURCE = {"lt_inner": "lt_kernels.hip", "ks_contig_inner": "ks_fused.hip",
+                 "ks_inner_tail": "ks_fused.hip",
                  "ks_moddown_strided": "ks_fused.hip", "ks_modup_strided": "ks_fused.hip",
                  "ks_moddown_tail": "ks_fused.hip", "ks_inner_gather": "ks_fused.hip",
                  "ks_intt_gather": "ks_fused.hip"}
@@ -481,24 +493,35 @@ def tiny_end_to_end(log, reps=50):
 def rotation_ceilings(ctx, prm, modes, log):
     """The two ceilings of one rotation at the top level (N = 2^16, L = 24,
     K = 8, dnum = 3): HBM (ciphertext in + key + ciphertext out at 8 TB/s) and
-    the vector-ALU integer rate (modular products per rotation over the
+    the vector ALU (modular products per rotation: those of moduli on doubles
+    at six FP64 operations each of the chip's full rate, the others at the
     device's measured Shoup-product rate), with the achieved fraction of each
     for the rotation modes without key reuse (R3) and with it (R2)."""
     n, L, K, dnum = prm["n"], len(prm["q"]), len(prm["p"]), prm["dnum"]
     alpha = -(-L // dnum)
     digits = -(-L // alpha)
-    ext = digits * (L + K) - L
-    ntts = L + ext + 2 * K + 2 * L                   # INTT d, NTT ext, INTT P, NTT conv
-    mulmods = (ntts * (n // 2) * (n.bit_length() - 1)          # butterflies
-               + digits * alpha * (L + K - alpha) * n + L * n   # ModUp BConv + digit scale
-               + 2 * K * L * n + 2 * K * n                      # ModDown BConv + scale
-               + 2 * digits * (L + K) * n                       # key inner product
-               + 2 * L * n)                                     # P^-1
+
+    def products(q, p):
+        """Modular products of the rows of q chain limbs q and special limbs p
+        (how many of each the arithmetic in question runs)."""
+        # INTT d, NTT ext (every digit's targets but its own limbs), INTT P,
+        # NTT conv
+        ntts = q + (digits - 1) * q + digits * p + 2 * p + 2 * q
+        return (ntts * (n // 2) * (n.bit_length() - 1)            # butterflies
+                + alpha * ((digits - 1) * q + digits * p) * n     # ModUp BConv
+                + q * n                                           # digit scale
+                + 2 * K * q * n + 2 * p * n                       # ModDown BConv + scale
+                + 2 * digits * (q + p) * n                        # key inner product
+                + 2 * q * n)                                      # P^-1
+
+    mulmods = products(L, K)
+    doubles = products(sum(map(on_doubles, prm["q"])), sum(map(on_doubles, prm["p"])))
     bytes_ = 8 * n * (2 * L + digits * 2 * (L + K) + 2 * L)
     rate = ctx.measure_mulmod_rate() * 1e12
     hbm = HBM_PEAK_GBS * 1e9 / bytes_
-    valu = rate / mulmods
+    valu = 1 / (doubles / FP64_MULMOD_PEAK + (mulmods - doubles) / rate)
     out = {"bytes_per_rotation": bytes_, "mulmods_per_rotation": mulmods,
+           "mulmods_on_doubles_per_rotation": doubles,
            "measured_shoup_mulmod_T_per_s": round(rate / 1e12, 3),
            "hbm_ceiling_rot_per_s": round(hbm, 1), "valu_ceiling_rot_per_s": round(valu, 1),
            "R3_frac_of_hbm": round(modes["R3_16ct_16_keys_rot_per_s"] / hbm, 4),
