@@ -55,6 +55,14 @@ struct KsGeom {
 // targets: halved, they still fill the chip twice over at the paired kernel's
 // occupancy (about 3 workgroups of 256 threads per CU)
 constexpr size_t kPairMinBlocks = 3072;
+// Rings whose conversions pair targets: strided passes of up to 256 points.  At
+// N = 2^17 the paired workgroup takes 88 KB of LDS and 251 VGPRs, one workgroup
+// of four wavefronts a CU, where the single-target one has sixteen: 16 rotations
+// of 6 limbs and 2 special primes 1565 us paired, 924 single (moduli of 55 bits),
+// 1169 and 796 (50 bits); with one twiddle table for both targets, which leaves
+// room for a second workgroup, 1544 and 1087.
+template <int LOGN>
+constexpr bool kPairs = split_a(LOGN) <= 8;
 // tiles up to which the inner products take two sets of wavefronts each: two
 // a CU.  One special basis of 8 limbs at N = 2^16 (512 tiles) 22.6 -> 18.9 us;
 // 24 limbs (1536 tiles) 45.9 -> 49.1 us, so larger launches do not.
@@ -880,7 +888,7 @@ int ks_modup(hck_context *ctx, const KsBatch &kb, const KsGeom &kg, uint64_t *ws
   // read of the digit's limbs for both); small launches keep one target per
   // workgroup and the kernel's lower register count
   const uint32_t targets = ctx->groups[0][level].second;
-  const bool paired = (size_t)targets * nb * GA::BLOCKS >= kPairMinBlocks;
+  const bool paired = kPairs<LOGN> && (size_t)targets * nb * GA::BLOCKS >= kPairMinBlocks;
   const auto gr = ctx->groups[paired][level];
   const ConvC *up_conv = ctx->d_up_conv + (size_t)level * kg.dnum * (kg.alpha + 1) * kg.nm;
   // algorithmic bytes: every digit limb is read once (the targets sharing it
@@ -899,10 +907,10 @@ int ks_modup(hck_context *ctx, const KsBatch &kb, const KsGeom &kg, uint64_t *ws
     kernel<<<grid, threads, 0, ctx->stream>>>(ws, groups, up_conv, kg, ctx->d_mod, ctx->d_tw);
   };
   if (!s30)
-    launch(paired ? k_modup_strided<LOGN, true, false> : k_modup_strided<LOGN, false, false>,
+    launch(paired ? k_modup_strided<LOGN, kPairs<LOGN>, false> : k_modup_strided<LOGN, false, false>,
            kNttThreads);
   else if (paired)
-    launch(k_modup_strided<LOGN, true, true>, kNttThreads);
+    launch(k_modup_strided<LOGN, kPairs<LOGN>, true>, kNttThreads);
   else
     launch(k_modup_strided<LOGN, false, true>, ConvPass<LOGN, false, true>::THREADS);
   timing_end(ctx);
@@ -935,7 +943,7 @@ int ks_down_conv(hck_context *ctx, uint32_t nb, const KsGeom &kg, uint64_t *ws, 
   }
   // in a launch large enough to fill the chip at half the workgroups, the K
   // special limbs are read once per pair of target limbs
-  const bool paired = (size_t)2 * nq * nb * GA::BLOCKS >= kPairMinBlocks;
+  const bool paired = kPairs<LOGN> && (size_t)2 * nq * nb * GA::BLOCKS >= kPairMinBlocks;
   const auto gr = ctx->down_groups[paired][kg.level];
   const ConvGroup *groups = ctx->d_groups + gr.first;
   const dim3 grid(GA::BLOCKS, 2 * gr.second, nb);
@@ -949,10 +957,10 @@ int ks_down_conv(hck_context *ctx, uint32_t nb, const KsGeom &kg, uint64_t *ws, 
                                               ctx->d_mod, ctx->d_tw);
   };
   if (!s30)
-    launch(paired ? k_moddown_strided<LOGN, true, false> : k_moddown_strided<LOGN, false, false>,
+    launch(paired ? k_moddown_strided<LOGN, kPairs<LOGN>, false> : k_moddown_strided<LOGN, false, false>,
            kNttThreads);
   else if (paired)
-    launch(k_moddown_strided<LOGN, true, true>, kNttThreads);
+    launch(k_moddown_strided<LOGN, kPairs<LOGN>, true>, kNttThreads);
   else
     launch(k_moddown_strided<LOGN, false, true>, ConvPass<LOGN, false, true>::THREADS);
   timing_end(ctx);

@@ -188,3 +188,29 @@ def test_small_switches_match_oracle(name, level, count, together):
     same(cts, want, "in place")
     ctx.relinearize_many(prods, rlk, outs=prods)
     same(prods, [o.relinearize(o.tensor(c, c), rlk_o) for c in cts_o], "relinearize in place")
+
+
+def test_largest_ring_batches_match_oracle():
+    """At N = 2^17 large launches too convert one target a workgroup (two take
+    LDS that leaves a CU one small workgroup); a batch of rotations is
+    bit-exact."""
+    taken, two_n = set(), 2 << 17
+    q = _primes(two_n, 1 << 60, 1, taken, -1) + _primes(two_n, 1 << 50, 5, taken, -1)
+    prm = dict(name="batch17", log_n=17, n=1 << 17, q=q, p=_primes(two_n, 1 << 60, 2, taken, -1),
+               dnum=3, scale=2.0 ** 40)
+    o, ctx = O.Oracle(prm), H.Context.from_params(prm)
+    sk, s_o = ctx.keygen_secret(1), o.keygen_secret(1)
+    g = o.galois_element(3)
+    gks, gko = ctx.keygen_rotation(sk, [3], 5), {g: o.keygen_galois(s_o, g, 5)}
+    r = S.uniform_residues(o.qmods(5), o.n, 44, 2)
+    cts = [ctx.ciphertext_import(r, 5, 2.0 ** 40) for _ in range(12)]
+    outs = [ctx.ciphertext() for _ in cts]
+    ctx.trace(True)
+    ctx.rotate_many(cts, 3, gks, outs=outs)
+    grids = {x[0]: x[1] for x in ctx.trace_read()}
+    ctx.trace(False)
+    # three digits of two limbs, each to the six other limbs
+    assert grids["ks_modup_strided"][1:] == (18, 12), grids
+    want = o.rotate(O.Ciphertext(r, 5, 2.0 ** 40), 3, gko).polys
+    for y in outs:
+        np.testing.assert_array_equal(ctx.ciphertext_export(y)[0], want)
