@@ -53,14 +53,16 @@ __device__ __forceinline__ void ntt_pass_body(uint64_t *buf, const LimbMap &map,
 #pragma unroll
       for (int v = 0; v < P; v++) x[v] = rf.canonical ? ar.load(u[v]) : Ar::raw(u[v]);
       const Tw *f = rf.rows + (size_t)k * G::R;
-      for (int i = threadIdx.x; i < G::R; i += G::THREADS) lf[i] = f[i];
+      constexpr bool ROWS_LDS = G::R <= 512;  // as the twiddles (TW_LDS)
+      if constexpr (ROWS_LDS)
+        for (int i = threadIdx.x; i < G::R; i += G::THREADS) lf[i] = f[i];
       __syncthreads();
       G::template inverse<Ar, twisted_bound<Ar>()>(lds, x, c, r, w, lw, ar);
       const uint64_t add = rf.add ? rf.add[k] : 0;
 #pragma unroll
       for (int i = 0; i < P; i++) {
         const int p = G::ipoint(r, i);
-        E y = ar.mul(x[i], lf[p]);
+        E y = ar.mul(x[i], ROWS_LDS ? lf[p] : f[p]);
         if (rf.add) y += ar.load(add);
         x_[G::gaddr(g, p)] = ar.template canon<3072>(y);
       }
@@ -77,14 +79,16 @@ __device__ __forceinline__ void ntt_pass_body(uint64_t *buf, const LimbMap &map,
   }
 }
 
+// A 1024-point pass is held to the registers of two workgroups a CU, like its
+// LDS (TW_LDS).
 template <int LOGR, int LOGN, bool STRIDED, bool INVERSE>
-__global__ __launch_bounds__((Pass<LOGR, LOGN, STRIDED>::THREADS)) void k_ntt_pass(
+__global__ __launch_bounds__((Pass<LOGR, LOGN, STRIDED>::THREADS), LOGR > 9 ? 2 : 1) void k_ntt_pass(
     uint64_t *buf, LimbMap map, const ModConst *__restrict__ mc, const Tw *__restrict__ w,
     const Tw *__restrict__ tt, RowFactors rf) {
   using G = Pass<LOGR, LOGN, STRIDED>;
   __shared__ uint64_t lds[G::LDS_WORDS];
   __shared__ Tw lw[G::TW_LEN];
-  __shared__ Tw lf[STRIDED && INVERSE ? G::R : 1];
+  __shared__ Tw lf[STRIDED && INVERSE && G::R <= 512 ? G::R : 1];
   // the data loads are issued before the modulus is known, so that their
   // latency and that of its constants overlap
   const uint64_t *in = buf + (size_t)map.row[blockIdx.y] * G::N;

@@ -214,3 +214,25 @@ def test_largest_ring_batches_match_oracle():
     want = o.rotate(O.Ciphertext(r, 5, 2.0 ** 40), 3, gko).polys
     for y in outs:
         np.testing.assert_array_equal(ctx.ciphertext_export(y)[0], want)
+
+
+@pytest.mark.parametrize("bits", [50, 57])
+def test_largest_ring_splits_match_oracle(bits):
+    """Every split of the full transforms at N = 2^17, the 1024-point pass
+    among them, on doubles and on integers: imports, products and exports."""
+    taken, two_n = set(), 2 << 17
+    q = _primes(two_n, 1 << 60, 1, taken, -1) + _primes(two_n, 1 << bits, 2, taken, -1)
+    prm = dict(name=f"splits17/{bits}", log_n=17, n=1 << 17, q=q, dnum=3, scale=2.0 ** 40,
+               p=_primes(two_n, 1 << 60, 1, taken, -1))
+    o, ctx = O.Oracle(prm), H.Context.from_params(prm)
+    tried = []
+    for i, split in enumerate((9, 8, 10)):
+        ctx.set_ntt_split(split)
+        tried.append(ctx.ntt_split())
+        for values in ("uniform", "top"):
+            r = _residues(o.qmods(2), o.n, values, 81 + i)
+            ct, ct_o = ctx.ciphertext_import(r, 2, 2.0 ** 40), O.Ciphertext(r, 2, 2.0 ** 40)
+            np.testing.assert_array_equal(ctx.ciphertext_export(ct)[0], r)
+            np.testing.assert_array_equal(ctx.ciphertext_export(ctx.mul(ct, ct))[0],
+                                          o.tensor(ct_o, ct_o).polys, f"{split}, {values}")
+    assert tried == [9, 8, 10]
